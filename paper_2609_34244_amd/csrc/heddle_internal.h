@@ -17,6 +17,7 @@ constexpr int kMaxMList = HEDDLE_MAX_MLIST;
 constexpr int64_t kLimit62 = int64_t(1) << 62;
 constexpr size_t kMaxLimitTable = size_t(256) << 20;       // bytes of the memory-limit table
 constexpr int64_t kMaxBandwidth = (int64_t(1) << 34) - 1;   // MB/s; keeps n * bw below 2^50
+constexpr int kSearchSlice = 512;                          // most templates of a wavefront's slice in the split search
 constexpr uint32_t kNarrowLimit = 0x7FFFFFFFu;   // exact 32-bit DP when every stage time is below this
 
 // a2a variant of a stage: no all-to-all (EP = 1), EP x TP group inside one
@@ -79,6 +80,22 @@ struct DevProfile {
     // copies exist only when the range proof allows narrowing
     const uint64_t *rows64[2];
     const uint32_t *rows32[2];
+    // split search: by kind, the index of (type, TP, EP), the row in the tables
+    // below (in entries) | the GPU type << 24, the row's bucket scale (fp32 bits)
+    // and its least layer time in two words (index 0: int64, 1: fp32 image, + 2
+    // for the 64-bit rows)
+    const uint4 *search_kind[4];     // [n_types * n_tp * n_ep]
+    // the tables, one block each, copied to LDS whole (index 0: int64 ns, 1:
+    // fp32 image; the 32-bit ones when the range proof allows):
+    // [search_rows][search_stride] {unused, P[0 .. L],
+    // the first index of every bucket (bytes)}, then
+    // [n_types * n_types + 1] p2p by type pair and a 0
+    const uint32_t *search32[2];
+    const uint64_t *search64[2];
+    int32_t search_buckets;
+    int32_t search_rows, search_stride[2];   // entries per row of the 32- and 64-bit tables
+    int32_t search_bytes32, search_bytes64;   // block sizes, multiples of 16
+    int32_t search_shift[2];         // 64-bit rows are bucketed by P >> shift
 };
 
 }  // namespace heddle
@@ -156,9 +173,27 @@ struct PriceArgs {
                                      // | in-flight class min(ceil(m / D), S) << 8 (0: memory ignored)
                                      // | rows of the windows W_1 .. W_{S-1} << 16 (status 0 only)
     uint16_t *wwin;                  // [n][n_m][win_stride(s_max)] window of stage s: first row | last row << 8
+    int32_t hard;                    // split kernel: only the templates that the search left,
+                                     // *(uint32_t *)iter of them, listed in peak_mem
     bool scratch_owned;              // host side: wst lives in a block of its own (hipStreamPerThread)
     unsigned char *ext_scratch;      // host side: a fixed device buffer for wst and wwin (no
     size_t ext_bytes;                // allocation, no profile buffer); NULL: the profile's buffer
+};
+
+// Launch constants of the split search.
+struct SearchArgs {
+    int32_t tab_bytes;               // bytes of the tables and kinds in LDS (0: read through the caches)
+    int32_t copy_bytes, kind_off, n_kinds;   // of them the tables; where the kinds follow; how many there are
+    int32_t wave_bytes;              // bytes of one wavefront's LDS region
+    int32_t s_cap;                   // stage columns: min(s_max, L)
+    int32_t slice;                   // templates per slice, 1 .. kSearchSlice
+    int32_t walk;                    // ends of a stage tried in one step when it is left no layer
+    int32_t sweeps;                  // sweeps after which a template is left to the split kernel
+    int32_t refill;                  // idle lanes at which a wavefront takes new templates
+    int32_t lim_bytes, lim_words, lim_rows, lim_f;   // memory limits in LDS: bytes, words per row, rows, in-flight counts
+    int32_t degrees;                 // (TP, EP) pairs: n_tp * n_ep
+    int32_t vec_rec, vec_lay;        // records / layer counts are read / stored 16 bytes at a time
+    int32_t words;                   // layer counts can be stored 4 bytes at a time
 };
 
 int validate_price_args(const heddle_profile *p, int64_t n, int32_t s_max, const uint8_t *d_n_stages,
@@ -166,6 +201,8 @@ int validate_price_args(const heddle_profile *p, int64_t n, int32_t s_max, const
 // count: 0 prices; 1 counts the relaxations over the windows; 2 counts those the
 // split kernel evaluates (it runs the DP); 1 and 2 write no plan outputs
 int launch_price(const heddle_profile *p, PriceArgs &a, hipStream_t stream, int count);
+// split search over the windows in a.wst / a.wwin (status, bottleneck, layers)
+int launch_search(const heddle_profile *p, const PriceArgs &a, bool narrow, hipStream_t stream);
 int launch_evaluate(const heddle_profile *p, const PriceArgs &a, hipStream_t stream);
 // window pass outputs: row stride of a plan's windows, in entries (a
 // multiple of 4, so that rows are stored 8 bytes at a time)

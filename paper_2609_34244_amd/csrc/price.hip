@@ -78,6 +78,8 @@ __device__ __forceinline__ void fetch_rows(RowRegs<V, NS> &r, const V *rows, uin
 // smallest admissible end keeping an optimal completion at every stage, i.e.
 // the lexicographically smallest optimal split.
 
+constexpr int64_t kSearchMin = 131072, kSearchMinF32 = 196608;  // templates from which the split search runs
+
 // MA: memory-aware (the flags do not ask to ignore memory); M1: one
 // micro-batch count per template. Compile-time choices, so that the hot
 // loops carry no test of them.
@@ -126,18 +128,29 @@ __global__ void __launch_bounds__(64, sizeof(V) == 4 ? 8 : 4) split_kernel(DevPr
         const uint32_t x = blockIdx.x & 7, j = blockIdx.x >> 3;
         t = (int64_t)((((j >> 6) << 3) + x) << 6) + (j & 63);
     }
+    // A.hard: only the templates that the split search left, from its list
+    const int64_t n_hard = A.hard ? (int64_t)*(const uint32_t *)A.iter : 0;
+    int64_t h = blockIdx.x;
+    auto next_hard = [&]() -> int64_t {
+        const int64_t i = h;
+        h += gridDim.x;
+        return i < n_hard ? A.peak_mem[i] : A.n;
+    };
+    if (A.hard) t = next_hard();
+    int64_t t_next = t;
     int S_next = 0;
     uint32_t rec_next = 0;
     if (t < A.n) {
         S_next = A.n_stages[t];
         rec_next = lane < A.s_max ? A.stages[t * A.s_max + lane] : 0u;
     }
-    for (; t < A.n; t += stride) {
+    for (; t < A.n; t = t_next) {
         const int S_in = S_next;
         const uint32_t rec_in = rec_next;
-        if (t + stride < A.n) {
-            S_next = A.n_stages[t + stride];
-            rec_next = lane < A.s_max ? A.stages[(t + stride) * A.s_max + lane] : 0u;
+        t_next = A.hard ? next_hard() : t + stride;
+        if (t_next < A.n) {
+            S_next = A.n_stages[t_next];
+            rec_next = lane < A.s_max ? A.stages[t_next * A.s_max + lane] : 0u;
         }
         const size_t obase = (size_t)t * n_m;
         // lane k: status of plan k after validation and windows (0: windows found),
@@ -592,6 +605,16 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     a.wwin = (uint16_t *)(buf + st_bytes);
     const int rw = launch_windows(p, a, w_lds, stream);
     if (rw != HEDDLE_OK) return rw;
+    // The split search takes batches that give its lanes enough templates; below
+    // that its chain of dependent steps, not the work, is what a call waits for
+    // (24,000 templates of c3: 205 us a call against 113 us with the recurrence; the two
+    // meet between 50,000 templates (c1) and 135,000 (c2, one micro-batch count), and
+    // with fp32 costs, which take a probe more, between 50,000 and 200,000)
+    a.hard = COUNT == 0 && a.n >= (F32 ? kSearchMinF32 : kSearchMin) ? 1 : 0;
+    if (a.hard) {
+        const int rs = launch_search(p, a, sizeof(V) == 4, stream);
+        if (rs != HEDDLE_OK) return rs;
+    }
     // at least 65,536 workgroups (one per template for a smaller batch) and at
     // least one per four templates, as a power of two: the hardware hands a
     // finished workgroup's slot to the next one, which evens out the
@@ -604,6 +627,7 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     const int64_t want = per_wg > floor_wg ? per_wg : floor_wg;
     int blocks = 1;
     while (blocks < want && blocks < (1 << 30)) blocks <<= 1;  // from 512 on, a multiple of 512: XCD-aware runs
+    if (a.hard) blocks = (int)(a.n < 8192 ? a.n : 8192);
     const DevProfile dev = p->dev;
     void *args[] = {(void *)&dev, (void *)&a};
     HEDDLE_HIP(hipLaunchKernel(kern, dim3(blocks), dim3(64 * wpb), args, lds, stream));

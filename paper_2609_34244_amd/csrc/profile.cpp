@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "heddle_internal.h"
@@ -478,8 +479,95 @@ extern "C" int heddle_load_profile(const heddle_profile_desc *d, heddle_profile 
             }
         }
 
+    // ---- split search: rows with a bucket index each, the p2p matrix, and by
+    // kind (type, TP, EP) the row and what the load of a template needs. An all-to-all variant beside
+    // "none" only exists when some EP degree is above 1.
+    const int NV = E == 1 && d->ep_degrees[0] == 1 ? 1 : 3;
+    // rows that valid records use, numbered in (type, TP, variant) order
+    std::vector<int32_t> s_row((size_t)N * K * NV, -1);
+    for (int g = 0; g < N; g++)
+        for (int k = 0; k < K; k++)
+            for (int e = 0; e < E; e++)
+                if (d->profiled[(size_t)g * K + k] && d->tp_degrees[k] <= d->node_size[g])
+                    s_row[((size_t)g * K + k) * NV + (NV == 1 ? 0 : a2a_variant(d->ep_degrees[e], d->tp_degrees[k], d->node_size[g]))] = 0;
+    int s_rows = 0;
+    for (int32_t &x : s_row) if (x == 0) x = s_rows++;
+    const int s_buckets = (size_t)s_rows * 256 <= 16384 ? 256 : 128;
+    dp.search_buckets = s_buckets;
+    std::vector<int32_t> kind_row((size_t)N * K * E, 0);       // row index; kinds no valid record has: 0
+    for (int g = 0; g < N; g++)
+        for (int k = 0; k < K; k++)
+            for (int e = 0; e < E; e++) {
+                const int var = NV == 1 ? 0 : a2a_variant(d->ep_degrees[e], d->tp_degrees[k], d->node_size[g]);
+                kind_row[(size_t)(g * K + k) * E + e] = std::max(s_row[(size_t)(g * K + k) * NV + var], 0);
+            }
+    std::vector<uint32_t> search_kind[4];
+    std::vector<uint64_t> search64[2];
+    std::vector<uint32_t> search32[2];
+    for (int v = 0; v < 2; v++) {
+        const std::vector<int64_t> &pp = v ? p2p_fx : p2p_ns;
+        uint64_t most = 1;
+        for (uint64_t x : rows64[v]) most = std::max(most, x);
+        int shift = 0;
+        while ((most >> shift) >= (uint64_t(1) << 32)) shift++;
+        dp.search_shift[v] = shift;
+        const bool narrow = v ? narrow_f32 : narrow_i64;
+        auto build = [&](auto &out, std::vector<uint32_t> &kinds) {
+            typedef typename std::remove_reference<decltype(out)>::type::value_type T;
+            // buckets 0 .. s_buckets (the last catches a rounded-up product), and an
+            // odd stride in words, which spreads the rows over the LDS banks
+            const size_t q_words = (s_buckets + 1 + sizeof(T) - 1) / sizeof(T);
+            size_t stride = 1 + R + q_words;
+            if (sizeof(T) == 4) stride |= 1;
+            dp.search_stride[sizeof(T) == 8] = (int32_t)stride;
+            std::vector<uint32_t> scales(std::max(s_rows, 1), 0);
+            std::vector<uint64_t> leasts(std::max(s_rows, 1), 0);
+            const size_t entries = (size_t)s_rows * stride + (size_t)N * N + 1;
+            out.assign((entries * sizeof(T) + 15) / 16 * 16 / sizeof(T), 0);
+            for (size_t x = 0; x < s_row.size(); x++) {
+                if (s_row[x] < 0) continue;
+                const int r = s_row[x];
+                const uint64_t *row = &rows64[v][(x / NV * 3 + x % NV) * R];
+                auto time_of = [&](uint64_t t) { return (float)(uint32_t)(t >> (sizeof(T) == 4 ? 0 : shift)); };
+                const float tot = time_of(row[L]);
+                const float scale = tot >= 1.f ? (float)(s_buckets - 1) / tot : 0.f;
+                uint64_t least = row[1] - row[0];
+                for (int l = 1; l < L; l++) least = std::min(least, row[l + 1] - row[l]);
+                std::memcpy(&scales[r], &scale, 4);
+                T *dst = &out[(size_t)r * stride];
+                leasts[r] = least;
+                for (int j = 0; j <= L; j++) dst[1 + j] = (T)row[j];
+                uint8_t *q = (uint8_t *)&dst[1 + R];
+                int i = 0;
+                for (int u = 0; u <= s_buckets; u++) {    // first index whose bucket is u or later
+                    while (i < L && (uint32_t)(time_of(row[i]) * scale) < (uint32_t)u) i++;
+                    q[u] = (uint8_t)i;
+                }
+            }
+            for (int x = 0; x < N * N; x++) out[(size_t)s_rows * stride + x] = (T)pp[x];
+            kinds.resize(kind_row.size() * 4);
+            for (size_t x = 0; x < kind_row.size(); x++) {
+                kinds[4 * x] = (uint32_t)(kind_row[x] * stride) | (uint32_t)(x / ((size_t)K * E)) << 24;
+                kinds[4 * x + 1] = scales[kind_row[x]];
+                kinds[4 * x + 2] = (uint32_t)leasts[kind_row[x]];
+                kinds[4 * x + 3] = (uint32_t)(leasts[kind_row[x]] >> 32);
+            }
+        };
+        if (narrow) build(search32[v], search_kind[v]);
+        if (v == 0 || fx_ok) build(search64[v], search_kind[v + 2]);
+        for (auto *x : {&search_kind[v], &search_kind[v + 2], &search32[v]})
+            if (x->empty()) x->assign(1, 0);
+        if (search64[v].empty()) search64[v].assign(1, 0);
+    }
+    dp.search_rows = s_rows;
+    dp.search_bytes64 = (int32_t)(search64[0].size() * 8);
+    dp.search_bytes32 = (int32_t)(std::max(search32[0].size(), search32[1].size()) * 4);
+
     // ---- upload
     Builder B;
+    const size_t o_sk[4] = {B.add(search_kind[0]), B.add(search_kind[1]), B.add(search_kind[2]), B.add(search_kind[3])},
+                 o_s64a = B.add(search64[0]), o_s64b = B.add(search64[1]),
+                 o_s32a = B.add(search32[0]), o_s32b = B.add(search32[1]);
     const size_t o_r64a = B.add(rows64[0]), o_r64b = B.add(rows64[1]), o_r32a = B.add(rows32[0]),
                  o_r32b = B.add(rows32[1]);
     size_t o_time = B.add(pre_time), o_time_fx = B.add(pre_time_fx), o_moe = B.add(pre_moe),
@@ -539,6 +627,11 @@ extern "C" int heddle_load_profile(const heddle_profile_desc *d, heddle_profile 
     dp.rows64[1] = (const uint64_t *)(base + o_r64b);
     dp.rows32[0] = (const uint32_t *)(base + o_r32a);
     dp.rows32[1] = (const uint32_t *)(base + o_r32b);
+    for (int x = 0; x < 4; x++) dp.search_kind[x] = (const uint4 *)(base + o_sk[x]);
+    dp.search64[0] = (const uint64_t *)(base + o_s64a);
+    dp.search64[1] = (const uint64_t *)(base + o_s64b);
+    dp.search32[0] = (const uint32_t *)(base + o_s32a);
+    dp.search32[1] = (const uint32_t *)(base + o_s32b);
     dp.n_f = F;
     dp.lim_stride = RL;
     p->dev = dp;

@@ -51,12 +51,6 @@ struct StageK {
     int32_t W, n_moe, inflight, etp, g, ki, node, i0, j0, pad;
 };
 
-// set lanes of a wavefront mask below this lane
-__device__ __forceinline__ int lanes_below(uint64_t m)
-{
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
 // time and synchronisation of a list entry, read together
 template <class TT> struct alignas(2 * sizeof(TT)) TGPair {
     TT x, y;

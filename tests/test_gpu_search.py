@@ -1,0 +1,93 @@
+"""The split search (batches of at least 131,072 templates, 196,608 with fp32
+costs) against the oracle: small batches whose every template the oracle
+prices, repeated to a batch that takes the search. Every copy has to equal
+the oracle's outputs bit for bit."""
+import numpy as np
+import pytest
+
+from gpu_common import CO, F32, assert_same, gpu_price, oracle_price
+from workloads.gen import Workload, make_workload, pack_stage, random_instance
+
+pytestmark = pytest.mark.gpu
+N = 196_608 + 77                                   # past both thresholds, no multiple of a slice
+
+
+@pytest.fixture(scope="module")
+def H():
+    import torch
+    assert torch.cuda.is_available(), "no GPU"
+    from paper_2609_34244_amd import heddle
+    heddle.lib()
+    return heddle
+
+
+def check(H, w, flags, ctx):
+    o = oracle_price(w, flags)
+    reps = -(-N // w.n)
+    order = np.random.default_rng(5).permutation(np.tile(np.arange(w.n), reps)[:N])
+    big = Workload(name=w.name, profile=w.profile, n_stages=np.ascontiguousarray(w.n_stages[order]),
+                   stages=np.ascontiguousarray(w.stages[order]), m=w.m, s_max=w.s_max)
+    g = gpu_price(H, H.heddle_load_profile(w.profile), big, flags)
+    assert_same(g, {k: v[order] for k, v in o.items()}, flags, ctx)
+    return o
+
+
+@pytest.mark.parametrize("flags", [0, CO, F32, F32 | CO])
+def test_random_instances(H, flags):
+    """ties, every status, stages that no layer fits, memory that binds, odd
+    stage slots, several in-flight classes"""
+    seen = set()
+    for seed in range(12):
+        w = random_instance(900 + seed, s_max=[6, 5, 4, 13, 16, 3][seed % 6], L=None if seed % 2 else 20 + seed, n=60,
+                            max_cost=6 if seed % 3 else 4000, cap_scale=[None, 0.5, 2.0][seed % 3])
+        seen |= set(np.unique(check(H, w, flags, f"seed {seed} flags {flags}")["status"]).tolist())
+    assert 0 in seen and 8 in seen
+
+
+@pytest.mark.parametrize("name,n", [("c2_7b_dense", 500), ("c3_70b_dense", 200), ("c4_moe", 300), ("c5_stress", 60)])
+@pytest.mark.parametrize("flags", [0, F32])
+def test_configs(H, name, n, flags):
+    check(H, make_workload(name, n), flags, f"{name} flags {flags}")
+
+
+@pytest.mark.parametrize("flags", [0, CO, F32])
+def test_wide_costs(H, flags):
+    """stage times beyond 2^32: 64-bit rows, bucketed by their high bits"""
+    for seed, scale in ((3, 10**9), (4, 10**12 + 7)):
+        w = random_instance(seed, L=30, s_max=9, n=60, max_cost=3000)
+        w.profile.layer_ns = np.ascontiguousarray(w.profile.layer_ns * scale)
+        w.m = np.array([1, 7], np.int32)
+        check(H, w, flags, f"scale {scale} flags {flags}")
+
+
+@pytest.mark.parametrize("flags", [0, CO, F32])
+def test_tables_outside_lds(H, flags):
+    """more stage kinds than a byte holds, and tables too large for LDS: read
+    through the caches"""
+    rng = np.random.default_rng(11)
+    w = random_instance(21, L=200, n_types=200, s_max=12, n=80, moe=True, invalid_frac=0.1)
+    assert w.profile.n_types * len(w.profile.tp_degrees) * len(w.profile.ep_degrees) > 256
+    w.profile.mem_cap_bytes[:] = rng.integers(60, 2000, size=200)
+    check(H, w, flags, f"flags {flags}")
+
+
+def test_left_to_the_split_kernel(H):
+    """templates whose cuts move up one layer at a time, so that the search
+    gives them up: heavy layers that only the first stages' type can hold"""
+    w = random_instance(1, L=120, n_types=2, s_max=12, n=40, moe=False, invalid_frac=0.0, cap_scale=100.0)
+    rng = np.random.default_rng(2)
+    p = w.profile
+    p.profiled[:] = 1
+    p.layer_ns[0] = 10
+    p.layer_ns[1] = np.where(rng.random(120) < 0.5, 10, 1000 + np.arange(120))[None, :]
+    p.mem_cap_bytes[:] = 1 << 40
+    p.node_size[:] = 8
+    p.n_gpus[:] = 4096
+    p.link_bw_MBps[:] = 1000
+    p.boundary_bytes = 0
+    S = rng.integers(8, 13, size=40)
+    g = rng.integers(0, 2, size=(40, 12))
+    w.n_stages = S.astype(np.uint8)
+    w.stages = np.ascontiguousarray(np.where(np.arange(12)[None] < S[:, None], pack_stage(g, 0, 0, 1), 0).astype(np.uint32))
+    check(H, w, 0, "heavy layers")
+    check(H, w, F32, "heavy layers, fp32")
