@@ -27,7 +27,9 @@
 // largest stage times, memories and synchronisation terms with their stages:
 // an alternative that moves the cut after stage b changes stages b and b+1
 // only, and the largest value over the other stages is the first of those
-// three not at b or b+1.
+// three not at b or b+1. The cost tables are read from a copy in LDS where it
+// leaves room for two workgroups on a CU (c3, 500,000 templates: 0.237 ms against
+// 0.283 ms through the caches).
 #include <cstring>
 
 #include "stage_cost.h"
@@ -58,18 +60,11 @@ template <class T> struct Top3 {
 
 template <bool F32> __device__ __forceinline__ uint64_t rounded(uint64_t T) { return F32 ? rne24(T) : T; }
 
-__device__ __forceinline__ int stage_prow(const DevProfile &P, uint32_t r)
-{
-    const int g = r & 0xFF, l2tp = (r >> 8) & 15, l2ep = (r >> 12) & 15;
-    const int ki = nibble(P.tp_index, l2tp);
-    return ((g * P.n_tp + ki) * 3 + a2a_variant(1 << l2ep, 1 << l2tp, P.node_size[g])) * (P.L + 1);
-}
-
 // COUNT: only count the stage-cost evaluations into A.work (S for the
 // proportional split, 2 per alternative priced)
 constexpr int kDistTpl = 256;                                  // most templates (and lanes) per workgroup
 
-template <bool F32, bool COUNT>
+template <bool F32, bool COUNT, class C>
 __global__ void __launch_bounds__(kDistTpl, 3) distribute_kernel(DevProfile P, PriceArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -79,7 +74,9 @@ __global__ void __launch_bounds__(kDistTpl, 3) distribute_kernel(DevProfile P, P
     const int nw = blockDim.x;                                 // templates per workgroup: 64, 128 or 256
     uint32_t *cnt = (uint32_t *)smem + tid;                    // [n_types][nw]: this lane's column
     uint8_t *cut = smem + (size_t)P.n_types * nw * 4 + tid;    // [s_cap + 1][nw]: stage starts c_0..c_S
-    auto C = [&](int s) -> int { return cut[s * nw]; };
+    C tab{P};                                                  // the cost block follows the columns
+    tab.load(smem + A.off_x);
+    auto cut_at = [&](int s) -> int { return cut[s * nw]; };
     const int L = P.L;
     const bool compute_only = (A.flags & HEDDLE_F_COMPUTE_ONLY) != 0;
     const bool word_layers = (A.s_max & 3) == 0 && ((uintptr_t)A.layers & 3) == 0;
@@ -134,13 +131,13 @@ __global__ void __launch_bounds__(kDistTpl, 3) distribute_kernel(DevProfile P, P
 
         // ---- proportional cuts: c_s = nearest integer to L * (speed of stages < s) / (speed of all)
         double total = 0.0;
-        for (int s = 0; s < S; s++) total += 1.0 / (double)P.rows64[0][stage_prow(P, rec[s]) + L];
+        for (int s = 0; s < S; s++) total += tab.inv_total(rec[s]);
         {
             double below = 0.0;
             int prev = 0;
             cut[0] = 0;
             for (int s = 1; s < S; s++) {
-                below += 1.0 / (double)P.rows64[0][stage_prow(P, rec[s - 1]) + L];
+                below += tab.inv_total(rec[s - 1]);
                 int c = (int)floor((double)L * below / total + 0.5);
                 c = c < prev + 1 ? prev + 1 : c;
                 c = c > L - (S - s) ? L - (S - s) : c;
@@ -160,7 +157,7 @@ __global__ void __launch_bounds__(kDistTpl, 3) distribute_kernel(DevProfile P, P
 #pragma unroll 1
             for (int s = 0; s < S; s++) {
                 const int g_next = s + 1 < S ? (int)(rec[s + 1] & 0xFF) : 0;
-                const StageCost c = stage_cost<F32>(P, rec[s], g_next, s, S, C(s), C(s + 1), D, Mp);
+                const StageCost c = stage_cost<F32>(tab, rec[s], g_next, s, S, cut_at(s), cut_at(s + 1), D, Mp);
                 const uint64_t T = rounded<F32>(c.T);
                 sumT += T;
                 tT.push(T, s);
@@ -183,9 +180,9 @@ __global__ void __launch_bounds__(kDistTpl, 3) distribute_kernel(DevProfile P, P
                 for (int b = 0; b + 1 < S; b++) {
                     const uint32_t rb = rec[b], rb1 = rec[b + 1];
                     const int g2 = b + 2 < S ? (int)(rec[b + 2] & 0xFF) : 0;
-                    const int lo = C(b), cb = C(b + 1), hi = C(b + 2);
-                    const uint64_t Tb = rounded<F32>(stage_cost<F32>(P, rb, (int)(rb1 & 0xFF), b, S, lo, cb, D, Mp).T);
-                    const uint64_t Tb1 = rounded<F32>(stage_cost<F32>(P, rb1, g2, b + 1, S, cb, hi, D, Mp).T);
+                    const int lo = cut_at(b), cb = cut_at(b + 1), hi = cut_at(b + 2);
+                    const uint64_t Tb = rounded<F32>(stage_cost<F32>(tab, rb, (int)(rb1 & 0xFF), b, S, lo, cb, D, Mp).T);
+                    const uint64_t Tb1 = rounded<F32>(stage_cost<F32>(tab, rb1, g2, b + 1, S, cb, hi, D, Mp).T);
                     const uint64_t T_rest = tT.without(b);
                     const int64_t M_rest = tM.without(b), G_rest = tG.without(b);
                     const bool others_fit = (nf & ~(3ull << b)) == 0;
@@ -197,8 +194,8 @@ __global__ void __launch_bounds__(kDistTpl, 3) distribute_kernel(DevProfile P, P
                             work += 2;
                             continue;
                         }
-                        const StageCost c0 = stage_cost<F32>(P, rb, (int)(rb1 & 0xFF), b, S, lo, c, D, Mp);
-                        const StageCost c1 = stage_cost<F32>(P, rb1, g2, b + 1, S, c, hi, D, Mp);
+                        const StageCost c0 = stage_cost<F32>(tab, rb, (int)(rb1 & 0xFF), b, S, lo, c, D, Mp);
+                        const StageCost c1 = stage_cost<F32>(tab, rb1, g2, b + 1, S, c, hi, D, Mp);
                         const uint64_t t0 = rounded<F32>(c0.T), t1 = rounded<F32>(c1.T);
                         const uint64_t B2 = max(T_rest, max(t0, t1));
                         const uint64_t sum2 = sumT - Tb - Tb1 + t0 + t1;
@@ -230,8 +227,8 @@ __global__ void __launch_bounds__(kDistTpl, 3) distribute_kernel(DevProfile P, P
             // layer counts; the winning alternative moves the start of stage best_b + 1
             auto layers_of = [&](int s) -> uint32_t {
                 if (!has_split || s >= S) return 0u;
-                const int a = s == best_b + 1 ? best_c : C(s);
-                const int e = s == best_b ? best_c : C(s + 1);
+                const int a = s == best_b + 1 ? best_c : cut_at(s);
+                const int e = s == best_b ? best_c : cut_at(s + 1);
                 return (uint32_t)(e - a);
             };
             if (word_layers) {
@@ -263,23 +260,29 @@ int launch_distribute(const heddle_profile *p, PriceArgs &a, hipStream_t stream,
     const size_t per_lane = (size_t)p->dev.n_types * 4 + (size_t)(s_cap + 1);
     int nw = kDistTpl;
     while (nw > 64 && (per_lane * nw > 63 * 1024 || a.n < (int64_t)nw * 4 * (cus > 0 ? cus : 1))) nw >>= 1;
-    const size_t lds = per_lane * nw;
+    const bool f32 = a.flags & HEDDLE_F_FP32, narrow = f32 ? p->narrow_f32 : p->narrow_i64;
+    // the cost block in LDS after the columns, once per workgroup: not where that leaves
+    // fewer than two workgroups on a CU
+    const size_t cols = (per_lane * nw + 15) & ~size_t(15), cost = cost_lds(p->dev, f32, max_lds);
+    const bool in_lds = cost && 2 * (cols + cost) <= (size_t)max_lds;
+    const size_t lds = cols + (in_lds ? cost : 0);
     if (lds > (size_t)max_lds) return fail(HEDDLE_E_RANGE, "per-lane tables of this profile do not fit in LDS");
-    const int64_t want = (a.n + nw - 1) / nw;
-    const int blocks = (int)(want < 65536 ? want : 65536);
-    const bool f32 = a.flags & HEDDLE_F_FP32;
-    const void *fn = count_only ? (f32 ? (const void *)distribute_kernel<true, true> : (const void *)distribute_kernel<false, true>)
-                                : (f32 ? (const void *)distribute_kernel<true, false> : (const void *)distribute_kernel<false, false>);
+    a.off_x = (int32_t)cols;
+    const int64_t want = (a.n + nw - 1) / nw, most = in_lds ? 6 * (int64_t)(cus > 0 ? cus : 1) * (kDistTpl / nw) : 65536;
+    const int blocks = (int)(want < most ? want : most);
+    const void *fn;
+    if (count_only)                                            // counts walk the same splits; speed is no matter
+        fn = f32 ? (const void *)distribute_kernel<true, true, GlobalCost<true>> : (const void *)distribute_kernel<false, true, GlobalCost<false>>;
+    else if (!in_lds)
+        fn = f32 ? (const void *)distribute_kernel<true, false, GlobalCost<true>> : (const void *)distribute_kernel<false, false, GlobalCost<false>>;
+    else if (f32)
+        fn = narrow ? (const void *)distribute_kernel<true, false, LdsCost<true, uint32_t>> : (const void *)distribute_kernel<true, false, LdsCost<true, uint64_t>>;
+    else
+        fn = narrow ? (const void *)distribute_kernel<false, false, LdsCost<false, uint32_t>> : (const void *)distribute_kernel<false, false, LdsCost<false, uint64_t>>;
     if (lds > 65536) HEDDLE_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    if (count_only) {
-        if (f32) hipLaunchKernelGGL((distribute_kernel<true, true>), dim3(blocks), dim3(nw), lds, stream, p->dev, a);
-        else hipLaunchKernelGGL((distribute_kernel<false, true>), dim3(blocks), dim3(nw), lds, stream, p->dev, a);
-    } else if (f32) {
-        hipLaunchKernelGGL((distribute_kernel<true, false>), dim3(blocks), dim3(nw), lds, stream, p->dev, a);
-    } else {
-        hipLaunchKernelGGL((distribute_kernel<false, false>), dim3(blocks), dim3(nw), lds, stream, p->dev, a);
-    }
-    HEDDLE_HIP(hipGetLastError());
+    const DevProfile dev = p->dev;
+    void *args[] = {(void *)&dev, (void *)&a};
+    HEDDLE_HIP(hipLaunchKernel(fn, dim3(blocks), dim3(nw), args, lds, stream));
     return HEDDLE_OK;
 }
 

@@ -30,6 +30,7 @@ __host__ __device__ inline int a2a_variant(int ep, int tp, int node)
 
 // Device-resident derived tables of one profile. Passed by value to kernels.
 // Prefix rows have L + 1 entries: row[j] = sum over layers l < j.
+struct CostKind;
 struct DevProfile {
     int32_t L, n_types, n_tp, n_ep;
     int32_t fx_exp;                  // fixed-point unit of the fp32 variant is 2^fx_exp
@@ -96,6 +97,21 @@ struct DevProfile {
     int32_t search_rows, search_stride[2];   // entries per row of the 32- and 64-bit tables
     int32_t search_bytes32, search_bytes64;   // block sizes, multiples of 16
     int32_t search_shift[2];         // 64-bit rows are bucketed by P >> shift
+    // stage costs (stage_cost.h), one block each (index 0: int64, 1: fp32 image),
+    // copied to LDS whole where it fits: CostKind by kind, p2p by type pair, the
+    // {state, expert gradient} and {activation, dense gradient} pairs, then the
+    // time rows that valid records use (32-bit entries when the range proof allows)
+    const unsigned char *cost_block[2];
+    int32_t cost_bytes[2];           // multiples of 16
+    int32_t cost_p2p, cost_sx, cost_ag, cost_rows;   // byte offsets
+};
+
+// What a stage's cost reads by its kind (type, TP, EP).
+struct CostKind {
+    int64_t cap, intra, link;        // memory, intra-node and same-type inter-node bandwidth
+    double inv_total;                // 1 / the int64 time of all layers (Distribute's speed)
+    uint32_t row, sx, ag;            // first entry of its time row and of its pair rows
+    int32_t node;                    // GPUs of the type's largest node
 };
 
 }  // namespace heddle

@@ -553,18 +553,56 @@ extern "C" int heddle_load_profile(const heddle_profile_desc *d, heddle_profile 
                 kinds[4 * x + 3] = (uint32_t)(leasts[kind_row[x]] >> 32);
             }
         };
-        if (narrow) build(search32[v], search_kind[v]);
-        if (v == 0 || fx_ok) build(search64[v], search_kind[v + 2]);
+        if (narrow) build(search32[v], search_kind[v]);        // one of the two widths is read
+        else if (v == 0 || fx_ok) build(search64[v], search_kind[v + 2]);
         for (auto *x : {&search_kind[v], &search_kind[v + 2], &search32[v]})
             if (x->empty()) x->assign(1, 0);
         if (search64[v].empty()) search64[v].assign(1, 0);
     }
     dp.search_rows = s_rows;
-    dp.search_bytes64 = (int32_t)(search64[0].size() * 8);
+    dp.search_bytes64 = (int32_t)(std::max(search64[0].size(), search64[1].size()) * 8);
     dp.search_bytes32 = (int32_t)(std::max(search32[0].size(), search32[1].size()) * 4);
+
+    // ---- stage costs in one block
+    std::vector<unsigned char> cost[2];
+    for (int v = 0; v < 2; v++) {
+        auto up16 = [](size_t x) { return (x + 15) & ~size_t(15); };
+        const size_t n_kinds = (size_t)N * K * E;
+        const size_t o_p2p = up16(n_kinds * sizeof(CostKind)), o_sx = up16(o_p2p + (size_t)N * N * 8),
+                     o_ag = o_sx + pair_sx.size() * 8, o_rows = o_ag + pair_ag.size() * 8;
+        const bool narrow = v ? narrow_f32 : narrow_i64;
+        dp.cost_p2p = (int32_t)o_p2p;
+        dp.cost_sx = (int32_t)o_sx;
+        dp.cost_ag = (int32_t)o_ag;
+        dp.cost_rows = (int32_t)o_rows;
+        cost[v].assign(up16(o_rows + (size_t)s_rows * R * (narrow ? 4 : 8)), 0);
+        unsigned char *c = cost[v].data();
+        for (int g = 0; g < N; g++)
+            for (int k = 0; k < K; k++)
+                for (int e = 0; e < E; e++) {
+                    const size_t kind = (size_t)(g * K + k) * E + e;
+                    const int var = a2a_variant(d->ep_degrees[e], d->tp_degrees[k], d->node_size[g]);
+                    const CostKind ck = {d->mem_cap_bytes[g], d->intra_bw_MBps[g], d->link_bw_MBps[(size_t)g * N + g],
+                                         1.0 / (double)rows64[0][(((size_t)g * K + k) * 3 + var) * R + L],
+                                         (uint32_t)(kind_row[kind] * R), (uint32_t)((k * E + e) * R), (uint32_t)(k * R),
+                                         d->node_size[g]};
+                    std::memcpy(c + kind * sizeof(CostKind), &ck, sizeof(ck));
+                }
+        std::memcpy(c + o_p2p, v ? p2p_fx.data() : p2p_ns.data(), (size_t)N * N * 8);
+        std::memcpy(c + o_sx, pair_sx.data(), pair_sx.size() * 8);
+        std::memcpy(c + o_ag, pair_ag.data(), pair_ag.size() * 8);
+        for (size_t x = 0; x < s_row.size(); x++) {
+            if (s_row[x] < 0) continue;
+            const size_t from = (x / NV * 3 + x % NV) * R, to = (size_t)s_row[x] * R;
+            if (narrow) std::memcpy(c + o_rows + to * 4, &rows32[v][from], R * 4);
+            else std::memcpy(c + o_rows + to * 8, &rows64[v][from], R * 8);
+        }
+        dp.cost_bytes[v] = (int32_t)cost[v].size();
+    }
 
     // ---- upload
     Builder B;
+    const size_t o_cost[2] = {B.add(cost[0]), B.add(cost[1])};
     const size_t o_sk[4] = {B.add(search_kind[0]), B.add(search_kind[1]), B.add(search_kind[2]), B.add(search_kind[3])},
                  o_s64a = B.add(search64[0]), o_s64b = B.add(search64[1]),
                  o_s32a = B.add(search32[0]), o_s32b = B.add(search32[1]);
@@ -632,6 +670,7 @@ extern "C" int heddle_load_profile(const heddle_profile_desc *d, heddle_profile 
     dp.search64[1] = (const uint64_t *)(base + o_s64b);
     dp.search32[0] = (const uint32_t *)(base + o_s32a);
     dp.search32[1] = (const uint32_t *)(base + o_s32b);
+    for (int v = 0; v < 2; v++) dp.cost_block[v] = base + o_cost[v];
     dp.n_f = F;
     dp.lim_stride = RL;
     p->dev = dp;
