@@ -91,3 +91,16 @@ def test_left_to_the_split_kernel(H):
     w.stages = np.ascontiguousarray(np.where(np.arange(12)[None] < S[:, None], pack_stage(g, 0, 0, 1), 0).astype(np.uint32))
     check(H, w, 0, "heavy layers")
     check(H, w, F32, "heavy layers, fp32")
+
+
+@pytest.mark.parametrize("chunk", [1, 15, 16, 17, 100, 0])
+def test_count_of_fitting_plans(H, chunk):
+    """the OK count of an enumerated space over chunks whose plan counts are and
+    are not multiples of 16"""
+    w = make_workload("c3_70b_dense", 1)
+    prof = H.heddle_load_profile(w.profile)
+    spec = H.EnumSpec(2, [0, 5], [0, 1, 2], [1, 2])
+    ns, st = H.heddle_enum_templates(spec, 0, H.heddle_enum_count(spec))
+    m = [8, 64, 65]
+    out = H.heddle_price_plans(prof, ns, st, m, 0, H.alloc_outputs(len(ns), 3, 2, 0))
+    assert H.heddle_best_enumerated(prof, spec, m, 0, chunk)[3] == int((out["status"] == 0).sum())
