@@ -189,12 +189,25 @@ struct PriceArgs {
                                      // | in-flight class min(ceil(m / D), S) << 8 (0: memory ignored)
                                      // | rows of the windows W_1 .. W_{S-1} << 16 (status 0 only)
     uint16_t *wwin;                  // [n][n_m][win_stride(s_max)] window of stage s: first row | last row << 8
-    int32_t hard;                    // split kernel: only the templates that the search left,
-                                     // *(uint32_t *)iter of them, listed in peak_mem
+    uint32_t *left;                  // templates that the split search left to the split kernel: how many
+                                     // (zeroed by the window pass), then their indices (left_bytes(n) bytes);
+                                     // NULL: no search ran, the split kernel takes every template
     bool scratch_owned;              // host side: wst lives in a block of its own (hipStreamPerThread)
     unsigned char *ext_scratch;      // host side: a fixed device buffer for wst and wwin (no
     size_t ext_bytes;                // allocation, no profile buffer); NULL: the profile's buffer
 };
+
+// The list of the templates that the split search leaves lies in scratch beside
+// the windows, not in the caller's outputs, and both its sides are bounded by the
+// batch: calls whose device work overlaps on one scratch buffer get undefined
+// outputs, but no store or load outside of their buffers.
+__host__ __device__ inline size_t left_bytes(int64_t n) { return ((size_t)n + 1) * 4; }
+__host__ __device__ inline int64_t left_template(const uint32_t *left, int64_t i, int64_t n)   // n: past the end
+{
+    if (i >= n || i >= (int64_t)left[0]) return n;
+    const int64_t t = left[1 + i];
+    return t < n ? t : n;
+}
 
 // Launch constants of the split search.
 struct SearchArgs {

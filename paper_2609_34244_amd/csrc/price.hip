@@ -128,15 +128,14 @@ __global__ void __launch_bounds__(64, sizeof(V) == 4 ? 8 : 4) split_kernel(DevPr
         const uint32_t x = blockIdx.x & 7, j = blockIdx.x >> 3;
         t = (int64_t)((((j >> 6) << 3) + x) << 6) + (j & 63);
     }
-    // A.hard: only the templates that the split search left, from its list
-    const int64_t n_hard = A.hard ? (int64_t)*(const uint32_t *)A.iter : 0;
+    // A.left: only the templates that the split search left, from its list
     int64_t h = blockIdx.x;
-    auto next_hard = [&]() -> int64_t {
+    auto next_left = [&]() -> int64_t {
         const int64_t i = h;
         h += gridDim.x;
-        return i < n_hard ? A.peak_mem[i] : A.n;
+        return left_template(A.left, i, A.n);
     };
-    if (A.hard) t = next_hard();
+    if (A.left) t = next_left();
     int64_t t_next = t;
     int S_next = 0;
     uint32_t rec_next = 0;
@@ -147,7 +146,7 @@ __global__ void __launch_bounds__(64, sizeof(V) == 4 ? 8 : 4) split_kernel(DevPr
     for (; t < A.n; t = t_next) {
         const int S_in = S_next;
         const uint32_t rec_in = rec_next;
-        t_next = A.hard ? next_hard() : t + stride;
+        t_next = A.left ? next_left() : t + stride;
         if (t_next < A.n) {
             S_next = A.n_stages[t_next];
             rec_next = lane < A.s_max ? A.stages[t_next * A.s_max + lane] : 0u;
@@ -593,25 +592,29 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     const size_t plans = (size_t)a.n * a.n_m;
     const size_t st_bytes = (plans * sizeof(uint32_t) + 255) & ~size_t(255);
     const size_t bytes = window_scratch_bytes(a.n, a.n_m, a.s_max);
+    // The split search takes batches that give its lanes enough templates; below
+    // that its chain of dependent steps, not the work, is what a call waits for
+    // (24,000 templates of c3: 205 us a call against 113 us with the recurrence; the two
+    // meet between 50,000 templates (c1) and 135,000 (c2, one micro-batch count), and
+    // with fp32 costs, which take a probe more, between 50,000 and 200,000). Its list
+    // holds 32-bit template indices
+    const bool search = COUNT == 0 && a.n >= (F32 ? kSearchMinF32 : kSearchMin) && a.n < (int64_t)UINT32_MAX;
     unsigned char *buf = nullptr;
     if (a.ext_scratch) {
         if (bytes > a.ext_bytes) return fail(HEDDLE_E_RANGE, "window scratch exceeds the fixed buffer");
         buf = a.ext_scratch;
+        a.left = search ? (uint32_t *)(buf + a.ext_bytes) : nullptr;   // a part of its own: see kNoallocLeftBytes
     } else {
-        const int rs = profile_scratch(p, stream, bytes, (void **)&buf, &a.scratch_owned);
+        // the list follows the windows (whose rows are multiples of 8 bytes)
+        const int rs = profile_scratch(p, stream, bytes + (search ? left_bytes(a.n) : 0), (void **)&buf, &a.scratch_owned);
         if (rs != HEDDLE_OK) return rs;
+        a.left = search ? (uint32_t *)(buf + bytes) : nullptr;
     }
     a.wst = (uint32_t *)buf;
     a.wwin = (uint16_t *)(buf + st_bytes);
     const int rw = launch_windows(p, a, w_lds, stream);
     if (rw != HEDDLE_OK) return rw;
-    // The split search takes batches that give its lanes enough templates; below
-    // that its chain of dependent steps, not the work, is what a call waits for
-    // (24,000 templates of c3: 205 us a call against 113 us with the recurrence; the two
-    // meet between 50,000 templates (c1) and 135,000 (c2, one micro-batch count), and
-    // with fp32 costs, which take a probe more, between 50,000 and 200,000)
-    a.hard = COUNT == 0 && a.n >= (F32 ? kSearchMinF32 : kSearchMin) ? 1 : 0;
-    if (a.hard) {
+    if (search) {
         const int rs = launch_search(p, a, sizeof(V) == 4, stream);
         if (rs != HEDDLE_OK) return rs;
     }
@@ -627,7 +630,7 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     const int64_t want = per_wg > floor_wg ? per_wg : floor_wg;
     int blocks = 1;
     while (blocks < want && blocks < (1 << 30)) blocks <<= 1;  // from 512 on, a multiple of 512: XCD-aware runs
-    if (a.hard) blocks = (int)(a.n < 8192 ? a.n : 8192);
+    if (search) blocks = (int)(a.n < 8192 ? a.n : 8192);
     const DevProfile dev = p->dev;
     void *args[] = {(void *)&dev, (void *)&a};
     HEDDLE_HIP(hipLaunchKernel(kern, dim3(blocks), dim3(64 * wpb), args, lds, stream));
@@ -648,6 +651,7 @@ int launch_price(const heddle_profile *p, PriceArgs &a, hipStream_t stream, int 
     if (!a.ext_scratch) lock.lock();
     a.wst = nullptr;
     a.wwin = nullptr;
+    a.left = nullptr;
     a.scratch_owned = false;
     int rc;
     if (count == 1) rc = launch_split<uint64_t, false, 1>(p, a, stream);
@@ -661,6 +665,7 @@ int launch_price(const heddle_profile *p, PriceArgs &a, hipStream_t stream, int 
     }
     a.wst = nullptr;
     a.wwin = nullptr;
+    a.left = nullptr;
     return rc;
 }
 
@@ -734,7 +739,11 @@ extern "C" int heddle_count_work(const heddle_profile *p, int64_t n, int32_t s_m
 // the array's name as a device address: the address of each GPU's copy is
 // taken once per device with hipGetSymbolAddress (with that device current)
 // and kept below.
-static __device__ __align__(256) unsigned char scratch[HEDDLE_NOALLOC_SCRATCH_BYTES];
+// The split search's list has a part of its own behind the windows', so that the
+// batches that fit do not depend on it: a plan takes at least 12 bytes of windows
+// (status word and one row of four).
+constexpr size_t kNoallocLeftBytes = ((size_t)HEDDLE_NOALLOC_SCRATCH_BYTES / 12 + 2) * 4;
+static __device__ __align__(256) unsigned char scratch[HEDDLE_NOALLOC_SCRATCH_BYTES + kNoallocLeftBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;

@@ -460,13 +460,16 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
             }
             const uint64_t hm = ballot(hard);
             if (hm) {
-                // a search that takes its cuts up layer by layer: left to the split kernel, on a
-                // list in the peak-memory outputs whose length is in the first iteration time
-                // (Evaluate writes both later)
+                // a search that takes its cuts up layer by layer: left to the split kernel,
+                // without a split until then (Evaluate reads no layers of such a plan,
+                // also when an overlapping call on this scratch loses the entry)
                 uint32_t at = 0;
-                if (lane == 0) at = atomicAdd((uint32_t *)A.iter, (uint32_t)__popcll(hm));
-                at = (uint32_t)uni((int)at);
-                if (hard) A.peak_mem[at + lanes_below(hm)] = t;
+                if (lane == 0) at = atomicAdd(A.left, (uint32_t)__popcll(hm));
+                at = (uint32_t)uni((int)at) + (uint32_t)lanes_below(hm);
+                if (hard) {
+                    if ((int64_t)at < A.n) A.left[1 + (size_t)at] = (uint32_t)t;
+                    for (int k = 0; k < A.n_m; k++) A.status[t * A.n_m + k] = (uint8_t)HEDDLE_S_OOM;
+                }
             }
         }
     }

@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(kWinTpl) window_kernel(DevProfile P, PriceArgs
     const int ws = win_stride(A.s_max);
     const bool mem_aware = (A.flags & HEDDLE_F_COMPUTE_ONLY) == 0;
     for (int g = 0; g < P.n_types; g++) cnt[g * nw] = 0;
-    if (blockIdx.x == 0 && tid == 0 && A.iter) *(uint32_t *)A.iter = 0;   // length of the split search's list
+    if (blockIdx.x == 0 && tid == 0 && A.left) A.left[0] = 0;  // length of the split search's list
 
     for (int64_t t0 = (int64_t)blockIdx.x * nw; t0 < A.n; t0 += (int64_t)gridDim.x * nw) {
         // ---------------- the records of templates t0 .. t0 + nw - 1 into LDS, and

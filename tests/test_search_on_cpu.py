@@ -1,0 +1,78 @@
+"""The split search, run on the CPU from its own source (cpu_lanes): against the
+oracle, and what it does where the GPU could not be asked without a fault."""
+import ctypes as C
+from concurrent.futures import ProcessPoolExecutor
+from multiprocessing import get_context
+
+import numpy as np
+import pytest
+
+import cpu_lanes as CL
+from oracle import oracle as O
+from workloads.gen import Workload, make_workload, random_instance
+
+CO, F32 = O.F_COMPUTE_ONLY, O.F_FP32
+
+
+def guarded(*args, **kw):
+    """cpu_lanes.split in a process of its own: an access outside of the buffers
+    ends that process and fails the test"""
+    CL.lib()
+    with ProcessPoolExecutor(1, mp_context=get_context("fork")) as ex:
+        return ex.submit(CL.split, *args, **kw).result()
+
+
+def repeated(w, n):
+    """a batch of n templates in a fixed order out of a smaller one"""
+    order = np.random.default_rng(5).permutation(np.arange(n) % w.n)
+    return Workload(name=w.name, profile=w.profile, n_stages=np.ascontiguousarray(w.n_stages[order]),
+                    stages=np.ascontiguousarray(w.stages[order]), m=w.m, s_max=w.s_max)
+
+
+@pytest.fixture(scope="module")
+def slow_links():
+    """the 70B-like cluster with links 40 times slower: many templates are left to the split kernel"""
+    w = make_workload("c3_70b_dense", 700)
+    w.profile.link_bw_MBps = np.maximum(w.profile.link_bw_MBps // 40, 1)
+    return w
+
+
+def test_left_list_holds_what_it_should(slow_links):
+    g = guarded(slow_links)
+    assert CL.assert_split(slow_links, g, 0) == g["left_count"] > 20
+    assert len(set(g["left"].tolist())) == g["left_count"]
+    assert (g["status"][g["left"]] == 8).all()                 # no split until the split kernel finds one
+
+
+def test_left_list_is_bounded(slow_links):
+    """a call that overlaps on the same scratch may write any value where the
+    list's length is kept (536,418,584: an iteration time of this profile, once
+    found there): nothing is stored beyond the list"""
+    n = slow_links.n
+    for preset in (536_418_584, n - 1, n, 2**32 - 3):
+        g = guarded(slow_links, preset=preset)
+        assert g["rc"] == 0 and g["broken"] is None
+        assert (g["left_count"] - preset) % 2**32 > 20
+
+
+def test_left_list_reads_are_bounded():
+    """the split kernel's side: a length or an entry beyond the batch ends the walk"""
+    L = CL.lib()
+    entry = lambda count, first, i, n: L.lanes_left_template(
+        np.array([count, first] + [7] * 8, np.uint32).ctypes.data_as(C.c_void_p), i, n)
+    assert entry(3, 5, 0, 9) == 5 and entry(3, 5, 2, 9) == 7
+    assert entry(3, 5, 3, 9) == 9                              # past the length
+    assert entry(536_418_584, 5, 9, 9) == 9                    # past the list
+    assert entry(1, 9, 0, 9) == 9 and entry(1, 2**32 - 1, 0, 9) == 9
+
+
+@pytest.mark.parametrize("flags", [0, CO])
+def test_random_instances(flags):
+    seen = set()
+    for seed in range(12):
+        w = repeated(random_instance(900 + seed, s_max=[6, 5, 4, 13, 16, 3][seed % 6], L=None if seed % 2 else 20 + seed,
+                                     n=60, max_cost=6 if seed % 3 else 4000, cap_scale=[None, 0.5, 2.0][seed % 3]), 300)
+        g = CL.split(w, flags)
+        CL.assert_split(w, g, flags, f"seed {seed} flags {flags}")
+        seen |= set(np.unique(g["status"]).tolist())
+    assert 0 in seen and len(seen) > 4
