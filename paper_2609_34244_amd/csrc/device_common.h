@@ -4,6 +4,12 @@
 #include "exact_math.h"
 #include "heddle_internal.h"
 
+// A condition that a kernel relies on: no code on the GPU; a CPU build of the
+// kernel defines it to check it.
+#ifndef HEDDLE_INVARIANT
+#define HEDDLE_INVARIANT(c) ((void)0)
+#endif
+
 namespace heddle {
 
 // LDS writes of a wavefront become visible to its other lanes

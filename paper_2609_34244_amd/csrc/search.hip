@@ -246,8 +246,9 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                     load = next_key >= 0;
                     key = load ? next_key : key;
                 }
-                last_probe = again;
-                warm = load && !again && found && !f32;
+                // (a lane whose probe is under way keeps what it is)
+                last_probe = state == kRun ? last_probe : again;
+                warm = state == kRun ? warm : load && !again && found && !f32;
                 state = ended && !load ? kEmpty : state;
                 const uint64_t empty = ballot(state == kEmpty);
                 const int at = head + lanes_below(empty);
@@ -349,7 +350,7 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                     bf = vmin<V>(vmax<V>(bf, least), b_max);
                     bf = warm ? hi_out : bf;
                     B = last_probe ? (V)vmin<uint64_t>(rne24_top((uint64_t)hi_out), (uint64_t)b_max) : bf;
-                    lo = last_probe ? (V)0 : least;
+                    lo = least;
                     hi = last_probe ? hi_out : INF;
                 }
                 wave_sync();
@@ -357,6 +358,9 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                 u_max = uni(wave_max(state == kRun ? S : 0));
             }
             // ---------------- a sweep: one step per stage, the last first
+            // no bound is below a stage's p2p and least layer time, so its row holds an index
+            // with P[row] >= B's remainder at or before its end: the lookup stays in the row
+            HEDDLE_INVARIANT(state != kRun || B >= least);
             int e = L, upe = L, lu = state == kRun ? S : 0;    // lu: steps of this lane
             bool fail = false, redo = false;
             V mx = 0;
@@ -385,6 +389,7 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                     const float fs = __uint_as_float(kd.y);
                     const V tt = pe > B ? (V)(pe - B) : (V)0;  // low_s: the first row with P[row] >= tt
                     const uint32_t bu = (uint32_t)((float)(uint32_t)(tt >> shift) * fs);
+                    HEDDLE_INVARIANT(tt <= tab[row + (uint32_t)e] && bu <= (uint32_t)P.search_buckets);
                     const int qi = ((const uint8_t *)&tab[row + (uint32_t)(L + 1)])[bu];
                     const int base = max((int)((w >> shc) & 255u), il);
                     int i = max(base, qi);

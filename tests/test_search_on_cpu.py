@@ -66,7 +66,20 @@ def test_left_list_reads_are_bounded():
     assert entry(1, 9, 0, 9) == 9 and entry(1, 2**32 - 1, 0, 9) == 9
 
 
-@pytest.mark.parametrize("flags", [0, CO])
+@pytest.mark.parametrize("flags", [F32, F32 | CO])
+def test_bounds_of_running_probes(slow_links, flags):
+    """fp32 costs: lanes that take new templates while others are inside the probe
+    of the rounded bound, p2p times above the layers' times: no bound falls below
+    the least a stage can take, so no lookup leaves its row"""
+    for w in [slow_links] + [random_instance(900 + seed, s_max=[6, 5, 4, 13, 16, 3][seed % 6], L=None if seed % 2 else 20 + seed,
+                                             n=60, max_cost=6 if seed % 3 else 4000, cap_scale=[None, 0.5, 2.0][seed % 3])
+                             for seed in (0, 4, 5, 7)]:
+        w = repeated(w, 1000)
+        g = CL.split(w, flags)
+        CL.assert_split(w, g, flags, f"{w.name} flags {flags}")
+
+
+@pytest.mark.parametrize("flags", [0, CO, F32, F32 | CO])
 def test_random_instances(flags):
     seen = set()
     for seed in range(12):
