@@ -225,13 +225,24 @@ struct SearchArgs {
     int32_t words;                   // layer counts can be stored 4 bytes at a time
 };
 
+struct SearchPlan {
+    SearchArgs x;
+    bool lt;                         // tables in LDS
+    int waves, per_cu, blocks;       // wavefronts per workgroup and resident on a CU, workgroups
+    size_t lds;                      // bytes per workgroup
+};
+
 int validate_price_args(const heddle_profile *p, int64_t n, int32_t s_max, const uint8_t *d_n_stages,
                         const uint32_t *d_stages, const int32_t *h_m, int32_t n_m, uint32_t flags);
 // count: 0 prices; 1 counts the relaxations over the windows; 2 counts those the
 // split kernel evaluates (it runs the DP); 1 and 2 write no plan outputs
 int launch_price(const heddle_profile *p, PriceArgs &a, hipStream_t stream, int count);
-// split search over the windows in a.wst / a.wwin (status, bottleneck, layers)
-int launch_search(const heddle_profile *p, const PriceArgs &a, bool narrow, hipStream_t stream);
+// split search over the windows in a.wst / a.wwin (status, bottleneck, layers):
+// where it runs on a CU with max_lds bytes of LDS for a workgroup and lds_cu for
+// all of them (false: it does not fit, the split kernel takes the whole batch),
+// then the launch
+bool place_search(const DevProfile &d, const PriceArgs &a, bool narrow, int max_lds, int lds_cu, int cus, SearchPlan &pl);
+int launch_search(const heddle_profile *p, const PriceArgs &a, const SearchPlan &pl, bool narrow, hipStream_t stream);
 int launch_evaluate(const heddle_profile *p, const PriceArgs &a, hipStream_t stream);
 // window pass outputs: row stride of a plan's windows, in entries (a
 // multiple of 4, so that rows are stored 8 bytes at a time)

@@ -598,7 +598,13 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     // meet between 50,000 templates (c1) and 135,000 (c2, one micro-batch count), and
     // with fp32 costs, which take a probe more, between 50,000 and 200,000). Its list
     // holds 32-bit template indices
-    const bool search = COUNT == 0 && a.n >= (F32 ? kSearchMinF32 : kSearchMin) && a.n < (int64_t)UINT32_MAX;
+    SearchPlan pl;
+    bool search = COUNT == 0 && a.n >= (F32 ? kSearchMinF32 : kSearchMin) && a.n < (int64_t)UINT32_MAX;
+    if (search) {
+        int cus = 0;
+        HEDDLE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+        search = place_search(p->dev, a, sizeof(V) == 4, max_lds, lds_cu, cus, pl);
+    }
     unsigned char *buf = nullptr;
     if (a.ext_scratch) {
         if (bytes > a.ext_bytes) return fail(HEDDLE_E_RANGE, "window scratch exceeds the fixed buffer");
@@ -615,7 +621,7 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     const int rw = launch_windows(p, a, w_lds, stream);
     if (rw != HEDDLE_OK) return rw;
     if (search) {
-        const int rs = launch_search(p, a, sizeof(V) == 4, stream);
+        const int rs = launch_search(p, a, pl, sizeof(V) == 4, stream);
         if (rs != HEDDLE_OK) return rs;
     }
     // at least 65,536 workgroups (one per template for a smaller batch) and at

@@ -509,22 +509,19 @@ static int launch_search_v(const heddle_profile *p, const PriceArgs &a, SearchAr
                     : launch_search_t<V, true, 2>(p, a, x, waves, blocks, lds, stream);
 }
 
-int launch_search(const heddle_profile *p, const PriceArgs &a, bool narrow, hipStream_t stream)
+bool place_search(const DevProfile &d, const PriceArgs &a, bool narrow, int max_lds, int lds_cu, int cus, SearchPlan &pl)
 {
-    const DevProfile &d = p->dev;
-    int lds_cu = 0, max_lds = 0, cus = 0;
-    HEDDLE_HIP(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, p->device));
-    HEDDLE_HIP(hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, p->device));
-    HEDDLE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    SearchArgs x;
-    std::memset(&x, 0, sizeof(x));
+    std::memset(&pl, 0, sizeof(pl));
+    SearchArgs &x = pl.x;
     x.s_cap = a.s_max < d.L ? a.s_max : d.L;
     const size_t tab = narrow ? (size_t)d.search_bytes32 : (size_t)d.search_bytes64;
     x.words = (a.s_max & 3) == 0 && ((uintptr_t)a.layers & 3) == 0;
     // tables in LDS while they leave room for wavefronts; kinds are bytes there
+    constexpr size_t kRoom = 4;
     x.n_kinds = d.n_types * d.n_tp * d.n_ep;
     const size_t kind_bytes = (size_t)x.n_kinds * 16;
-    const bool lt = x.n_kinds <= 256 && tab + kind_bytes + 4 * search_wave_bytes(x.s_cap, true) <= (size_t)max_lds;
+    const bool lt = x.n_kinds <= 256 && 256 + tab + kind_bytes + kRoom * search_wave_bytes(x.s_cap, true) <= (size_t)max_lds;
+    pl.lt = lt;
     x.kind_off = lt ? (int32_t)tab : 0;
     x.copy_bytes = lt ? (int32_t)tab : 0;
     x.tab_bytes = 256 + (lt ? (int32_t)(tab + kind_bytes) : 0);
@@ -532,13 +529,19 @@ int launch_search(const heddle_profile *p, const PriceArgs &a, bool narrow, hipS
     x.vec_rec = (a.s_max & 3) == 0 && ((uintptr_t)a.stages & 15) == 0;
     x.vec_lay = (a.s_max & 15) == 0 && ((uintptr_t)a.layers & 15) == 0;
     x.wave_bytes = (int32_t)search_wave_bytes(x.s_cap, lt);
-    // the memory limits too, when they fit a third of it
+    // the memory limits too, when they fit a third of it and leave the same room
+    // beside the tables
     x.lim_f = d.n_f < x.s_cap || !lt ? d.n_f : x.s_cap;
     x.lim_rows = x.n_kinds * x.lim_f;
     const int lim_words = ((d.L + 4) >> 2) | 1;                // odd: rows spread over the banks
-    if (lt && !(a.flags & HEDDLE_F_COMPUTE_ONLY) && (size_t)x.lim_rows * lim_words * 4 <= 56 * 1024) x.lim_words = lim_words;
-    else x.lim_f = d.n_f;
-    x.lim_bytes = (x.lim_rows * x.lim_words * 4 + 15) & ~15;
+    const size_t lim = ((size_t)x.lim_rows * lim_words * 4 + 15) & ~size_t(15);
+    if (lt && !(a.flags & HEDDLE_F_COMPUTE_ONLY) && lim <= 56 * 1024 &&
+        (size_t)x.tab_bytes + lim + kRoom * x.wave_bytes <= (size_t)max_lds) {
+        x.lim_words = lim_words;
+        x.lim_bytes = (int32_t)lim;
+    } else {
+        x.lim_f = d.n_f;
+    }
     // wavefronts per workgroup (the registers allow 16 per CU at the most): the count that puts most wavefronts on a CU
     int waves = 1, wgs = 0;
     const int cap = 16;
@@ -552,7 +555,7 @@ int launch_search(const heddle_profile *p, const PriceArgs &a, bool narrow, hipS
             waves = w;
         }
     }
-    if (wgs == 0) return fail(HEDDLE_E_RANGE, "stage columns of this s_max do not fit in LDS");
+    if (wgs == 0 || cus < 1) return false;
     const int per_cu = wgs * waves;
     // every wavefront one slice, or as few equal ones as fit its list
     const int64_t slots = (int64_t)cus * per_cu;
@@ -572,9 +575,17 @@ int launch_search(const heddle_profile *p, const PriceArgs &a, bool narrow, hipS
     // a CU's share of LDS each, so that no CU takes more workgroups than another: they are
     // resident all at once, and the one that takes longest ends the launch
     size_t lds = ((size_t)lds_cu / wgs) & ~size_t(511);
-    lds = lds < (size_t)max_lds ? lds : (size_t)max_lds;
-    return narrow ? launch_search_v<uint32_t>(p, a, x, lt, waves, (int)blocks, lds, stream)
-                  : launch_search_v<uint64_t>(p, a, x, lt, waves, (int)blocks, lds, stream);
+    pl.lds = lds < (size_t)max_lds ? lds : (size_t)max_lds;
+    pl.waves = waves;
+    pl.per_cu = per_cu;
+    pl.blocks = (int)blocks;
+    return true;
+}
+
+int launch_search(const heddle_profile *p, const PriceArgs &a, const SearchPlan &pl, bool narrow, hipStream_t stream)
+{
+    return narrow ? launch_search_v<uint32_t>(p, a, pl.x, pl.lt, pl.waves, pl.blocks, pl.lds, stream)
+                  : launch_search_v<uint64_t>(p, a, pl.x, pl.lt, pl.waves, pl.blocks, pl.lds, stream);
 }
 
 }  // namespace heddle

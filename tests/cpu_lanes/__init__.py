@@ -22,7 +22,7 @@ LDS = 160 * 1024
 
 class SplitRun(C.Structure):
     _fields_ = [("cus", C.c_int32), ("max_lds", C.c_int32), ("preset_on", C.c_int32), ("preset", C.c_uint32),
-                ("n_broken", C.c_int32), ("broken", C.c_char * 256)]
+                ("placed", C.c_int32), ("lt", C.c_int32), ("lim", C.c_int32), ("per_cu", C.c_int32), ("n_broken", C.c_int32), ("broken", C.c_char * 256)]
 
 
 def build():
@@ -86,7 +86,7 @@ def split(w, flags=0, cus=1, max_lds=LDS, preset=None):
     L.heddle_free_profile(h)
     return {"rc": rc, "error": err, "bottleneck": bn, "layers": ly, "status": st, "left_count": int(left[0]),
             "left": left[1:1 + min(int(left[0]), n)], "broken": r.broken.decode() if r.n_broken else None,
-            "n_broken": r.n_broken}
+            "n_broken": r.n_broken, "tables_in_lds": bool(r.lt), "limits_in_lds": bool(r.lim), "per_cu": r.per_cu}
 
 
 def assert_split(w, g, flags, ctx=""):

@@ -176,7 +176,8 @@ struct SplitRun {
     int32_t cus, max_lds;            // in: the device
     int32_t preset_on;               // in: another call writes `preset` where the list's length is kept,
     uint32_t preset;                 //     after the window pass
-    int32_t n_broken;                // out
+    int32_t placed, lt, lim, per_cu; // out: the search fits; tables, memory limits in LDS; wavefronts on a CU
+    int32_t n_broken;
     char broken[256];
 };
 
@@ -215,11 +216,17 @@ extern "C" int lanes_split(const heddle_profile *p, int64_t n, int32_t s_max, co
     a.wst = (uint32_t *)dev(plans * 4);
     a.wwin = (uint16_t *)dev(plans * win_stride(s_max) * 2);
     a.left = (uint32_t *)dev(left_bytes(n));
+    SearchPlan pl;
+    r->placed = place_search(p->dev, a, narrow, lanes::max_lds, lanes::max_lds, lanes::cus, pl);
+    r->lt = pl.lt;
+    r->lim = pl.x.lim_words > 0;
+    r->per_cu = pl.per_cu;
     size_t lds = 0;
-    int rc = prepare_windows(p, a, lanes::max_lds, &lds);
+    int rc = r->placed ? 0 : HEDDLE_E_RANGE;
+    if (!rc) rc = prepare_windows(p, a, lanes::max_lds, &lds);
     if (!rc) rc = launch_windows(p, a, lds, nullptr);
     if (!rc && r->preset_on) a.left[0] = r->preset;
-    if (!rc) rc = launch_search(p, a, narrow, nullptr);
+    if (!rc) rc = launch_search(p, a, pl, narrow, nullptr);
     memcpy(bottleneck, a.bottleneck, plans * t);
     memcpy(layers, a.layers, plans * s_max);
     memcpy(status, a.status, plans);

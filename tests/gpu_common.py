@@ -5,7 +5,7 @@ from __future__ import annotations
 import numpy as np
 
 from oracle import oracle as O
-from workloads.gen import Workload
+from workloads.gen import Workload, random_instance
 
 F32 = 1
 CO = 2
@@ -59,3 +59,16 @@ def key_lt(it_a, m_a, it_b, m_b):
     fa = Fraction(float(it_a)) if isinstance(it_a, (float, np.floating)) else int(it_a)
     fb = Fraction(float(it_b)) if isinstance(it_b, (float, np.floating)) else int(it_b)
     return fa * int(m_b) < fb * int(m_a)
+
+
+def large_profile(n_types, L, s_max, scale, n):
+    """every (type, TP) row in use, so that the search's tables come near LDS's size"""
+    seed = next(s for s in range(100) if len(random_instance(s, L=2, n_types=1, n=1).profile.tp_degrees) == 3)
+    w = random_instance(seed, L=L, n_types=n_types, s_max=s_max, n=n, max_cost=3000, moe=False, invalid_frac=0.1)
+    p = w.profile
+    p.profiled[:] = 1
+    p.node_size[:] = 8
+    p.n_gpus[:] = 64
+    p.layer_ns = np.ascontiguousarray(p.layer_ns * scale)
+    p.mem_cap_bytes[:] = np.random.default_rng(11).integers(L, 6 * L, size=n_types)
+    return w

@@ -5,7 +5,7 @@ the oracle's outputs bit for bit."""
 import numpy as np
 import pytest
 
-from gpu_common import CO, F32, assert_same, gpu_price, oracle_price
+from gpu_common import CO, F32, assert_same, gpu_price, large_profile, oracle_price
 from workloads.gen import Workload, make_workload, pack_stage, random_instance
 
 pytestmark = pytest.mark.gpu
@@ -69,6 +69,15 @@ def test_tables_outside_lds(H, flags):
     assert w.profile.n_types * len(w.profile.tp_degrees) * len(w.profile.ep_degrees) > 256
     w.profile.mem_cap_bytes[:] = rng.integers(60, 2000, size=200)
     check(H, w, flags, f"flags {flags}")
+
+
+@pytest.mark.parametrize("n_types,L,s_max,scale", [(61, 32, 8, 10**9), (22, 200, 4, 10**9), (51, 120, 3, 1), (20, 60, 12, 1)])
+def test_tables_near_the_size_of_lds(H, n_types, L, s_max, scale):
+    """memory limits that would fit LDS alone, but not beside the tables (the
+    last one: both fit)"""
+    w = large_profile(n_types, L, s_max, scale, 60)
+    for flags in (0, F32):
+        check(H, w, flags, f"{n_types} types, L {L}, flags {flags}")
 
 
 def test_left_to_the_split_kernel(H):

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import cpu_lanes as CL
+from gpu_common import large_profile
 from oracle import oracle as O
 from workloads.gen import Workload, make_workload, random_instance
 
@@ -89,3 +90,23 @@ def test_random_instances(flags):
         CL.assert_split(w, g, flags, f"seed {seed} flags {flags}")
         seen |= set(np.unique(g["status"]).tolist())
     assert 0 in seen and len(seen) > 4
+
+
+@pytest.mark.parametrize("flags", [0, F32])
+@pytest.mark.parametrize("n_types,L,s_max,scale,limits", [
+    (61, 32, 8, 10**9, False), (22, 200, 4, 10**9, False), (51, 120, 3, 1, False), (26, 96, 7, 10**9, True),
+    (20, 60, 12, 1, True), (85, 10, 5, 1, True)])
+def test_tables_and_limits_near_the_size_of_lds(n_types, L, s_max, scale, limits, flags):
+    """tables of 70 to 130 KB, memory limits that fit LDS alone but not beside
+    them: the search runs with at least four wavefronts on a CU"""
+    w = large_profile(n_types, L, s_max, scale, 100)
+    g = CL.split(w, flags)
+    CL.assert_split(w, g, flags, f"{n_types} types, L {L}")
+    assert g["tables_in_lds"] and g["limits_in_lds"] == limits and g["per_cu"] >= 4
+
+
+def test_search_without_room():
+    """LDS too small for one wavefront's columns: not placed, nothing enqueued"""
+    w = random_instance(3, L=100, s_max=64, n=4)
+    g = CL.split(w, 0, max_lds=16 * 1024)
+    assert g["rc"] == -4 and (g["left_count"], g["per_cu"]) == (0xA5A5A5A5, 0)
