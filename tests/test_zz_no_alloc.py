@@ -153,6 +153,7 @@ def test_noalloc_takes_no_device_memory(H, c3):
     s = torch.cuda.Stream()
     warm = H.heddle_load_profile(w.profile)
     H.heddle_price_plans_noalloc(warm, ns, st, m, 0, out)
+    s.wait_stream(torch.cuda.current_stream())                 # the calls share one scratch and one set of outputs
     H.heddle_price_plans_noalloc(warm, ns, st, m, 0, out, stream=s)
     torch.cuda.synchronize()
     prof = H.heddle_load_profile(w.profile)
