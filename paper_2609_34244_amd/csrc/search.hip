@@ -97,7 +97,8 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
     const uint4 *gkinds = P.search_kind[(f32 ? 1 : 0) + (sizeof(V) == 8 ? 2 : 0)];
     const uint4 *kinds = LT ? (const uint4 *)(smem + X.kind_off) : gkinds;
     uint8_t *degree = smem + X.tab_bytes - 256;                // [256] by log2 TP | log2 EP << 4: index of (TP, EP)
-    for (int i = threadIdx.x; i < 256; i += blockDim.x) degree[i] = (uint8_t)(nibble(P.tp_index, i & 15) * P.n_ep + nibble(P.ep_index, i >> 4));
+    for (int i = threadIdx.x; i < 256; i += blockDim.x)
+        degree[i] = (uint8_t)min(nibble(P.tp_index, i & 15) * P.n_ep + nibble(P.ep_index, i >> 4), X.degrees - 1);
     if constexpr (LT) {
         for (int i = threadIdx.x; i < X.n_kinds; i += blockDim.x) ((uint4 *)(smem + X.kind_off))[i] = gkinds[i];
     }
@@ -123,7 +124,12 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
     uint32_t *colW = (uint32_t *)(mine + 2 * kSearchSlice) + lane;
     uint32_t *colK = colW + (X.s_cap + 2) * 64;                // !LT: kind
 
+    // What is read from the window pass's scratch (which templates have windows, their
+    // in-flight classes and windows) may be another call's where calls overlap on one
+    // buffer: it is read once or bounded on use, so that whatever it holds, every
+    // access stays inside the batch and the tables, and every search ends.
     int state = kEmpty, S = 0, key = 0, k0 = 0, left = 0;
+    int f_top = 0;                                             // micro-batches in flight, less one, at most
     int64_t t = 0;
     bool last_probe = false;                                   // fp32: the probe that gives the split
     bool warm = false;                                         // a bound of an earlier class is being tested
@@ -157,16 +163,17 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
     float sw = 0.f, sp = 0.f;
     V least = 0;
     auto place = [&](int q0, uint4 r, uint32_t r4, uint2 w2) {
-        const uint32_t rr[5] = {r.x, r.y, r.z, r.w, r4};
+        const uint32_t rr[5] = {r.x, r.y, r.z, r.w, r4}, n_top = (uint32_t)N - 1;
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const int u = S - 1 - q0 - q;                      // below 0: past the last stage, into a spare row
             const bool in = u >= 0;
-            const uint32_t k = in ? (rr[q] & 255u) * (uint32_t)X.degrees + degree[(rr[q] >> 8) & 255u] : 0u;
+            const uint32_t g = min(rr[q] & 255u, n_top);
+            const uint32_t k = in ? g * (uint32_t)X.degrees + degree[(rr[q] >> 8) & 255u] : 0u;
             const uint4 kd = kinds[k];
-            const V p2p = pm[u > 0 ? (rr[q] & 255u) * N + (rr[q + 1] & 255u) : (uint32_t)(N * N)];
+            const V p2p = pm[u > 0 ? g * N + min(rr[q + 1] & 255u, n_top) : (uint32_t)(N * N)];
             const uint32_t w = ((q & 2) ? w2.y : w2.x) >> ((q & 1) * 16);
-            const uint32_t a = w & 255, b = (w >> 8) & 255;
+            const uint32_t a = min(w & 255, (uint32_t)L), b = min((w >> 8) & 255, (uint32_t)L);
             const float fs = in ? __uint_as_float(kd.y) : 0.f;
             sw += fs;
             sp += fs * (float)p2p;
@@ -189,12 +196,16 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                 if (q >= nt) return 0;
                 bool ok = false;
                 for (int k = 0; k < A.n_m; k++) ok |= (A.wst[(base_t + q) * A.n_m + k] & 255u) == HEDDLE_S_OK;
-                return ok ? (int)A.n_stages[base_t + q] : 0;
+                const int st = A.n_stages[base_t + q];
+                return ok && st <= X.s_cap ? st : 0;
             };
+            uint32_t has = 0;                                  // bit i: the template i * 64 + lane of the slice
+            static_assert(kSearchSlice <= 32 * 64, "a bit per 64 templates of a slice");
             bins[lane] = 0;
             wave_sync();
             for (int q0 = 0; q0 < nt; q0 += 64) {
                 const int st = usable(q0 + lane);
+                has |= (st ? 1u : 0u) << (q0 >> 6);
                 if (st) atomicAdd(&bins[64 - st], 1u);
             }
             wave_sync();
@@ -204,8 +215,8 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
             n_list = rl32(incl, 63);
             wave_sync();
             for (int q0 = 0; q0 < nt; q0 += 64) {
-                const int st = usable(q0 + lane);
-                if (!st) continue;
+                if (!((has >> (q0 >> 6)) & 1u)) continue;
+                const int st = A.n_stages[base_t + q0 + lane];
                 list[atomicAdd(&bins[64 - st], 1u)] = (uint16_t)(q0 + lane | (st - 1) << 10);
                 if (A.n_m == 1) continue;
                 for (int k = 0; k < A.n_m; k++) {              // plans without windows beside ones with
@@ -327,6 +338,7 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                     }
                 }
                 if (load) {
+                    f_top = max(key, 1) - 1;
                     sw = sp = 0.f;
                     least = 0;
                     place(0, r0, r1.x, w0);
@@ -382,7 +394,7 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                 if (on) {
                     const uint32_t row = (kd.x & 0xFFFFFFu) + 1;
                     int il = 0;
-                    const int f = min(u, key - 1);
+                    const int f = min(u, f_top);
                     if (mem_aware) il = lim_at(kind, f, e);
                     const V p2p = *pp;
                     const V pe = tab[row + (uint32_t)e] + p2p;

@@ -21,7 +21,7 @@ LDS = 160 * 1024
 
 
 class SplitRun(C.Structure):
-    _fields_ = [("cus", C.c_int32), ("max_lds", C.c_int32), ("preset_on", C.c_int32), ("preset", C.c_uint32),
+    _fields_ = [("cus", C.c_int32), ("max_lds", C.c_int32), ("preset_on", C.c_int32), ("preset", C.c_uint32), ("other", C.c_int32),
                 ("placed", C.c_int32), ("lt", C.c_int32), ("lim", C.c_int32), ("per_cu", C.c_int32), ("n_broken", C.c_int32), ("broken", C.c_char * 256)]
 
 
@@ -66,7 +66,7 @@ def lib():
     return _lib
 
 
-def split(w, flags=0, cus=1, max_lds=LDS, preset=None):
+def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0):
     """Window pass and split search over a workload. Returns the outputs that
     the search writes, `left` (the templates it left to the split kernel) and
     what it found broken (None: every stated condition held)."""
@@ -78,7 +78,7 @@ def split(w, flags=0, cus=1, max_lds=LDS, preset=None):
     t = np.float32 if flags & O.F_FP32 else np.int64
     bn, ly, st = np.empty((n, len(m)), t), np.empty((n, len(m), s_max), np.uint8), np.empty((n, len(m)), np.uint8)
     left = np.zeros(n + 1, np.uint32)
-    r = SplitRun(cus=cus, max_lds=max_lds, preset_on=preset is not None, preset=preset or 0)
+    r = SplitRun(cus=cus, max_lds=max_lds, preset_on=preset is not None, preset=preset or 0, other=other)
     d = lambda a: a.ctypes.data
     ns, recs = np.ascontiguousarray(w.n_stages, np.uint8), np.ascontiguousarray(w.stages, np.uint32)
     rc = L.lanes_split(h, n, s_max, d(ns), d(recs), d(m), len(m), flags, d(bn), d(ly), d(st), d(left), C.addressof(r))

@@ -69,6 +69,7 @@ static ucontext_t main_ctx;
 static int cur, block_alive, block_arrived;
 static uint64_t block_epoch, progress;
 static const std::function<void()> *body;
+static std::function<void()> meanwhile;                        // work of another call, now and then
 
 static void yield()
 {
@@ -82,6 +83,7 @@ const uint64_t *exchange(uint64_t v, uint64_t *present)
     Wave &w = waves[cur >> 6];
     const uint64_t e = w.epoch;
     const int par = e & 1;
+    if (meanwhile && progress % 997 == 0) meanwhile();
     w.buf[par][l] = v;
     w.there[par] |= uint64_t(1) << l;
     progress++;
@@ -176,6 +178,7 @@ struct SplitRun {
     int32_t cus, max_lds;            // in: the device
     int32_t preset_on;               // in: another call writes `preset` where the list's length is kept,
     uint32_t preset;                 //     after the window pass
+    int32_t other;                   // in: not 0: the seed of another call's window pass over the same scratch
     int32_t placed, lt, lim, per_cu; // out: the search fits; tables, memory limits in LDS; wavefronts on a CU
     int32_t n_broken;
     char broken[256];
@@ -226,7 +229,16 @@ extern "C" int lanes_split(const heddle_profile *p, int64_t n, int32_t s_max, co
     if (!rc) rc = prepare_windows(p, a, lanes::max_lds, &lds);
     if (!rc) rc = launch_windows(p, a, lds, nullptr);
     if (!rc && r->preset_on) a.left[0] = r->preset;
+    if (!rc && r->other) {
+        auto draw = [x = (uint64_t)(uint32_t)r->other]() mutable { return (uint32_t)((x = x * 6364136223846793005ull + 1442695040888963407ull) >> 33); };
+        lanes::meanwhile = [=]() mutable {
+            for (size_t o = 0; o < plans; o++) a.wst[o] = (draw() % 10 < 7 ? 0u : draw() % 9) | draw() << 8;
+            for (size_t o = 0; o < plans * win_stride(s_max); o++) a.wwin[o] = (uint16_t)draw();
+        };
+        lanes::meanwhile();
+    }
     if (!rc) rc = launch_search(p, a, pl, narrow, nullptr);
+    lanes::meanwhile = nullptr;
     memcpy(bottleneck, a.bottleneck, plans * t);
     memcpy(layers, a.layers, plans * s_max);
     memcpy(status, a.status, plans);

@@ -67,6 +67,22 @@ def test_left_list_reads_are_bounded():
     assert entry(1, 9, 0, 9) == 9 and entry(1, 2**32 - 1, 0, 9) == 9
 
 
+@pytest.mark.parametrize("flags", [0, CO, F32])
+@pytest.mark.parametrize("in_lds", [True, False])
+def test_windows_of_another_call(in_lds, flags):
+    """a call of another batch or flags that overlaps on the same scratch leaves
+    any status, in-flight class and window there, and calls templates valid that
+    are not: the search ends and stays inside its tables and buffers"""
+    for seed in range(1, 9):
+        w = random_instance(40 + seed, L=[9, 30, 200][seed % 3], n_types=3 if in_lds else 200, s_max=[5, 12, 16][seed % 3], n=300,
+                            max_cost=3000, moe=True, invalid_frac=0.6)
+        if seed % 2:
+            w.profile.layer_ns = np.ascontiguousarray(w.profile.layer_ns * 10**9)
+        w.n_stages[::7] = 255
+        g = guarded(w, flags, other=seed)
+        assert g["rc"] == 0 and g["broken"] is None, (seed, g["broken"])
+
+
 @pytest.mark.parametrize("flags", [F32, F32 | CO])
 def test_bounds_of_running_probes(slow_links, flags):
     """fp32 costs: lanes that take new templates while others are inside the probe
