@@ -205,9 +205,9 @@ void heddle_free_profile(heddle_profile *p);
  * slowest stage time.
  * Scratch: without DISTRIBUTE, about n * n_m * (4 + 2 * s_max) bytes (s_max
  * rounded up to a multiple of 4) for the per-plan validation and row
- * windows, and 4 * (n + 1) bytes more for a batch that takes the split search
- * (131,072 templates or more, 196,608 with FP32), in the profile's buffer of
- * `stream`.
+ * windows, and 4 * (n + 130) bytes more for a batch that may take the split
+ * search (131,072 templates or more, 196,608 with FP32), in the profile's buffer
+ * of `stream`.
  * Returns HEDDLE_OK, HEDDLE_E_INVAL, HEDDLE_E_RANGE (the iteration time could
  * exceed 2^62 for these m, or the fp32 costs span too wide a range to sum
  * exactly), HEDDLE_E_NOMEM (the scratch) or HEDDLE_E_DEVICE. With

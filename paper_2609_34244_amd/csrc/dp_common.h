@@ -5,6 +5,15 @@
 
 namespace heddle {
 
+// Whether a batch has enough templates for a search with a lane each, from the
+// counts of its sample: V templates with windows, of so many stages in all (where
+// the line lies, and why: launch_split).
+__device__ __forceinline__ bool search_runs(const PriceArgs &A, float V, float stages)
+{
+    const float slow = 4.f * (A.p2p_share * stages - 0.05f * V);       // V * the weight of transfers, 0 .. V
+    return V * V >= V * A.need + fminf(fmaxf(slow, 0.f), V) * A.need_slow;
+}
+
 template <class V> __device__ __forceinline__ const V *stage_rows(const DevProfile &P, bool f32);
 template <> __device__ __forceinline__ const uint32_t *stage_rows<uint32_t>(const DevProfile &P, bool f32)
 {

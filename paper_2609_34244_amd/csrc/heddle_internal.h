@@ -126,6 +126,7 @@ struct heddle_profile {
     int64_t max_ar_ns;               // bound on any stage's gradient synchronisation time
     int64_t max_ar_fx;               // the same, fp32-rounded, fixed-point units
     int64_t max_tiled_ns;            // bound on any stage time under any expert layout
+    float p2p_share;                 // the middle one of the p2p times over the middle one of the rows' times
     int64_t max_ar_tiled_ns;         // bound on any stage's synchronisation under any expert layout
     // Scratch of the pricing path, one buffer per stream, grown on demand and
     // kept until the profile is freed (a fresh stream-ordered block per call
@@ -189,9 +190,13 @@ struct PriceArgs {
                                      // | in-flight class min(ceil(m / D), S) << 8 (0: memory ignored)
                                      // | rows of the windows W_1 .. W_{S-1} << 16 (status 0 only)
     uint16_t *wwin;                  // [n][n_m][win_stride(s_max)] window of stage s: first row | last row << 8
-    uint32_t *left;                  // templates that the split search left to the split kernel: how many
-                                     // (zeroed by the window pass), then their indices (left_bytes(n) bytes);
-                                     // NULL: no search ran, the split kernel takes every template
+    // batches that may take the split search (else NULL: the split kernel takes every
+    // template): [0] how many templates the search left to the split kernel (zeroed by
+    // the window pass), [1] whether it ran (it says so itself), [2 ..] the templates with
+    // windows in each of kSamples workgroups of the window pass and [2 + kSamples ..]
+    // those templates' stages, from [kLeftHead] on the templates left (left_bytes(n) bytes)
+    uint32_t *left;
+    float need, need_slow, p2p_share;   // search_runs(); need 0: it runs, nothing is counted
     bool scratch_owned;              // host side: wst lives in a block of its own (hipStreamPerThread)
     unsigned char *ext_scratch;      // host side: a fixed device buffer for wst and wwin (no
     size_t ext_bytes;                // allocation, no profile buffer); NULL: the profile's buffer
@@ -201,11 +206,12 @@ struct PriceArgs {
 // the windows, not in the caller's outputs, and both its sides are bounded by the
 // batch: calls whose device work overlaps on one scratch buffer get undefined
 // outputs, but no store or load outside of their buffers.
-__host__ __device__ inline size_t left_bytes(int64_t n) { return ((size_t)n + 1) * 4; }
+constexpr int kSamples = 64, kLeftHead = 2 + 2 * kSamples;
+__host__ __device__ inline size_t left_bytes(int64_t n) { return ((size_t)n + kLeftHead) * 4; }
 __host__ __device__ inline int64_t left_template(const uint32_t *left, int64_t i, int64_t n)   // n: past the end
 {
     if (i >= n || i >= (int64_t)left[0]) return n;
-    const int64_t t = left[1 + i];
+    const int64_t t = left[kLeftHead + i];
     return t < n ? t : n;
 }
 
@@ -217,7 +223,7 @@ struct SearchArgs {
     int32_t s_cap;                   // stage columns: min(s_max, L)
     int32_t slice;                   // templates per slice, 1 .. kSearchSlice
     int32_t walk;                    // ends of a stage tried in one step when it is left no layer
-    int32_t sweeps;                  // sweeps after which a template is left to the split kernel
+    int32_t sweeps, sweeps_short;    // sweeps after which a template is left to the split kernel (short: up to 16 stages)
     int32_t refill;                  // idle lanes at which a wavefront takes new templates
     int32_t lim_bytes, lim_words, lim_rows, lim_f;   // memory limits in LDS: bytes, words per row, rows, in-flight counts
     int32_t degrees;                 // (TP, EP) pairs: n_tp * n_ep
@@ -250,6 +256,7 @@ __host__ __device__ inline int win_stride(int s_max) { return (s_max + 3) & ~3; 
 // window pass: LDS check and attribute set-up (nothing enqueued), then the launch
 int prepare_windows(const heddle_profile *p, const PriceArgs &a, int max_lds, size_t *lds);
 int launch_windows(const heddle_profile *p, const PriceArgs &a, size_t lds, hipStream_t stream);
+int window_blocks(const heddle_profile *p, const PriceArgs &a);   // its workgroups
 int launch_distribute(const heddle_profile *p, PriceArgs &a, hipStream_t stream, bool count_only);
 int launch_tile(const heddle_profile *p, const PriceArgs &a, uint8_t *tiling, hipStream_t stream);
 // expert tiling holds stage times and synchronisation values in 32 bits

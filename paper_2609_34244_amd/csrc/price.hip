@@ -78,7 +78,10 @@ __device__ __forceinline__ void fetch_rows(RowRegs<V, NS> &r, const V *rows, uin
 // smallest admissible end keeping an optimal completion at every stage, i.e.
 // the lexicographically smallest optimal split.
 
-constexpr int64_t kSearchMin = 131072, kSearchMinF32 = 196608;  // templates from which the split search runs
+// The split search: templates of a batch from which it may and does run, and templates with
+// windows from which it does (of at most 4 stages, of more; with slow links so many more)
+constexpr int64_t kSearchMin = 131072, kSearchMinF32 = 196608, kSearchSure = 786432;
+constexpr float kSearchWin4 = 32000, kSearchWin = 56000, kSearchSlow = 130000, kSearchSlowF32 = 250000;
 
 // MA: memory-aware (the flags do not ask to ignore memory); M1: one
 // micro-batch count per template. Compile-time choices, so that the hot
@@ -128,14 +131,15 @@ __global__ void __launch_bounds__(64, sizeof(V) == 4 ? 8 : 4) split_kernel(DevPr
         const uint32_t x = blockIdx.x & 7, j = blockIdx.x >> 3;
         t = (int64_t)((((j >> 6) << 3) + x) << 6) + (j & 63);
     }
-    // A.left: only the templates that the split search left, from its list
+    // listed: only the templates that the split search left, from its list
     int64_t h = blockIdx.x;
     auto next_left = [&]() -> int64_t {
         const int64_t i = h;
         h += gridDim.x;
         return left_template(A.left, i, A.n);
     };
-    if (A.left) t = next_left();
+    const bool listed = A.left && A.left[1] != 0;
+    if (listed) t = next_left();
     int64_t t_next = t;
     int S_next = 0;
     uint32_t rec_next = 0;
@@ -146,7 +150,7 @@ __global__ void __launch_bounds__(64, sizeof(V) == 4 ? 8 : 4) split_kernel(DevPr
     for (; t < A.n; t = t_next) {
         const int S_in = S_next;
         const uint32_t rec_in = rec_next;
-        t_next = A.left ? next_left() : t + stride;
+        t_next = listed ? next_left() : t + stride;
         if (t_next < A.n) {
             S_next = A.n_stages[t_next];
             rec_next = lane < A.s_max ? A.stages[t_next * A.s_max + lane] : 0u;
@@ -593,17 +597,37 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     const size_t st_bytes = (plans * sizeof(uint32_t) + 255) & ~size_t(255);
     const size_t bytes = window_scratch_bytes(a.n, a.n_m, a.s_max);
     // The split search takes batches that give its lanes enough templates; below
-    // that its chain of dependent steps, not the work, is what a call waits for
-    // (24,000 templates of c3: 205 us a call against 113 us with the recurrence; the two
-    // meet between 50,000 templates (c1) and 135,000 (c2, one micro-batch count), and
-    // with fp32 costs, which take a probe more, between 50,000 and 200,000). Its list
-    // holds 32-bit template indices
+    // that its chain of dependent steps, not the work, is what a call waits for.
+    // Two lines, measured with either kernel on the whole batch (us a call,
+    // recurrence / search; all with one micro-batch count unless they say so):
+    // - templates, known here: c2 85/121 at 65,536, 138/133 at 131,072, 247/154 at
+    //   262,144; c3 129/180, 219/193, 376/223; c4 117/141, 194/153, 346/172; c5 511/514,
+    //   910/594; fp32 costs, which take a probe more: c3 138/210, 230/229, 402/264;
+    // - templates with windows among them, which the window pass counts in a sample
+    //   (the search decides, and tells the split kernel, which has to be launched for
+    //   either answer): c3 of 262,144 templates with 70% more of them invalid (47,000
+    //   left) 181/192, of 524,288 (93,000) 313/239; c2 with 90% (47,000) 130/144, (90,000)
+    //   229/185. Where transfers weigh as much as layers, bounds settle between
+    //   neighbouring cuts, more templates are left to the split kernel, and the line
+    //   lies higher: links 40 times slower, c3 154,000 361/382, 308,000 654/578, c4
+    //   111,000 191/242, 223,000 333/311, with fp32 costs c3 308,000 777/798, 590,000
+    //   1421/1251; 10 times slower, c3 77,000 216/266, 154,000 374/335. The weight of
+    //   transfers is the middle p2p time times the stages of a template over the middle
+    //   time of a row (c1 .. c5 0.01 .. 0.02; 10 times slower 0.13 .. 0.21): none up to 0.05,
+    //   all from 0.3. Not counted from 786,432 templates on, where the search is not
+    //   slower with 90% invalid or slow links (c3 of 1,000,000: 336/289 and 1196/970).
+    // Its list holds 32-bit template indices
     SearchPlan pl;
     bool search = COUNT == 0 && a.n >= (F32 ? kSearchMinF32 : kSearchMin) && a.n < (int64_t)UINT32_MAX;
     if (search) {
         int cus = 0;
         HEDDLE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
         search = place_search(p->dev, a, sizeof(V) == 4, max_lds, lds_cu, cus, pl);
+        const int64_t wgs = window_blocks(p, a);
+        const float part = (float)(wgs < kSamples ? wgs : kSamples) / (float)wgs;
+        a.need = a.n >= kSearchSure ? 0.f : part * (a.s_cap <= 4 ? kSearchWin4 : kSearchWin);
+        a.need_slow = part * (F32 ? kSearchSlowF32 : kSearchSlow);
+        a.p2p_share = p->p2p_share;
     }
     unsigned char *buf = nullptr;
     if (a.ext_scratch) {
@@ -636,7 +660,12 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     const int64_t want = per_wg > floor_wg ? per_wg : floor_wg;
     int blocks = 1;
     while (blocks < want && blocks < (1 << 30)) blocks <<= 1;  // from 512 on, a multiple of 512: XCD-aware runs
-    if (search) blocks = (int)(a.n < 8192 ? a.n : 8192);
+    // beside a search: for the few templates it leaves, or for all of them. Idle
+    // workgroups cost about 6 us per 32,768 (c1, which leaves none, 131,072 templates: 55 us
+    // at 8,192, 56 at 16,384, 61 at 32,768, 67 at 65,536); few workgroups are uneven where the
+    // recurrence runs after all, the more stages the more (c3 with 90% invalid: 124, 116,
+    // 104, 103)
+    if (search) blocks = a.need == 0.f ? 8192 : a.s_cap > 12 ? 65536 : a.s_cap > 4 ? 32768 : 16384;
     const DevProfile dev = p->dev;
     void *args[] = {(void *)&dev, (void *)&a};
     HEDDLE_HIP(hipLaunchKernel(kern, dim3(blocks), dim3(64 * wpb), args, lds, stream));
@@ -748,7 +777,7 @@ extern "C" int heddle_count_work(const heddle_profile *p, int64_t n, int32_t s_m
 // The split search's list has a part of its own behind the windows', so that the
 // batches that fit do not depend on it: a plan takes at least 12 bytes of windows
 // (status word and one row of four).
-constexpr size_t kNoallocLeftBytes = ((size_t)HEDDLE_NOALLOC_SCRATCH_BYTES / 12 + 2) * 4;
+constexpr size_t kNoallocLeftBytes = ((size_t)HEDDLE_NOALLOC_SCRATCH_BYTES / 12 + kLeftHead) * 4;
 static __device__ __align__(256) unsigned char scratch[HEDDLE_NOALLOC_SCRATCH_BYTES + kNoallocLeftBytes];
 
 namespace {

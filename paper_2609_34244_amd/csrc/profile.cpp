@@ -501,6 +501,19 @@ extern "C" int heddle_load_profile(const heddle_profile_desc *d, heddle_profile 
                 const int var = NV == 1 ? 0 : a2a_variant(d->ep_degrees[e], d->tp_degrees[k], d->node_size[g]);
                 kind_row[(size_t)(g * K + k) * E + e] = std::max(s_row[(size_t)(g * K + k) * NV + var], 0);
             }
+    // how far transfers weigh in a stage's time
+    float p2p_share = 0.f;
+    {
+        auto middle = [](std::vector<int64_t> x) {
+            if (x.empty()) return int64_t(0);
+            std::nth_element(x.begin(), x.begin() + x.size() / 2, x.end());
+            return x[x.size() / 2];
+        };
+        std::vector<int64_t> tot;
+        for (size_t x = 0; x < s_row.size(); x++)
+            if (s_row[x] >= 0) tot.push_back((int64_t)rows64[0][(x / NV * 3 + x % NV) * R + L]);
+        p2p_share = (float)middle(p2p_ns) / (float)std::max<int64_t>(middle(tot), 1);
+    }
     std::vector<uint32_t> search_kind[4];
     std::vector<uint64_t> search64[2];
     std::vector<uint32_t> search32[2];
@@ -674,6 +687,7 @@ extern "C" int heddle_load_profile(const heddle_profile_desc *d, heddle_profile 
     dp.n_f = F;
     dp.lim_stride = RL;
     p->dev = dp;
+    p->p2p_share = p2p_share;
     p->max_stage_ns = (int64_t)max_stage;
     p->max_ar_ns = (int64_t)max_ar;
     p->max_tiled_ns = (int64_t)max_tiled;

@@ -77,6 +77,11 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
     const V INF = DPInf<V>::value;
     enum { kEmpty, kRun, kDone };                              // lane states
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    // the same answer in every wavefront; the split kernel reads it
+    bool runs = true;
+    if (A.need > 0.f) runs = search_runs(A, (float)wave_sum(A.left[2 + lane]), (float)wave_sum(A.left[2 + kSamples + lane]));
+    if (blockIdx.x == 0 && threadIdx.x == 0) A.left[1] = runs ? 1u : 0u;
+    if (!runs) return;
     const int L = P.L, RS = P.search_stride[sizeof(V) == 8], N = P.n_types, ls = P.lim_stride, F = P.n_f;
     const bool f32 = (A.flags & HEDDLE_F_FP32) != 0;
     constexpr bool mem_aware = LIM != 0;
@@ -353,7 +358,7 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                     }
                     par = shc = 0;
                     nb = INF;
-                    left = X.sweeps;
+                    left = S <= 16 ? X.sweeps_short : X.sweeps;
                     state = kRun;
                     // the first probe: the bound that an even division of the work would reach, or
                     // an earlier class's bound (this class fits wherever that one does)
@@ -484,7 +489,7 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
                 if (lane == 0) at = atomicAdd(A.left, (uint32_t)__popcll(hm));
                 at = (uint32_t)uni((int)at) + (uint32_t)lanes_below(hm);
                 if (hard) {
-                    if ((int64_t)at < A.n) A.left[1 + (size_t)at] = (uint32_t)t;
+                    if ((int64_t)at < A.n) A.left[kLeftHead + (size_t)at] = (uint32_t)t;
                     for (int k = 0; k < A.n_m; k++) A.status[t * A.n_m + k] = (uint8_t)HEDDLE_S_OOM;
                 }
             }
@@ -576,10 +581,14 @@ bool place_search(const DevProfile &d, const PriceArgs &a, bool narrow, int max_
     // new templates once 24 lanes are idle (16 and 32 are level within 2%); a template is left
     // to the split kernel after so many sweeps, where the lanes that wait for it cost more
     // than its recurrence: c3 (16 stages) 470 us a call at 12, 490 at 18, 560 at 30, c5 (32
-    // stages, 300,000 templates) 3.4 ms at 12, 3.0 at 18, 3.3 at 24
+    // stages, 300,000 templates) 3.4 ms at 12, 3.0 at 18, 3.3 at 24. By the template's own
+    // stages: c2 in 64 stage slots 161 us at 12, 183 at 18 (131,072 templates; 138 with the
+    // recurrence); but 18 for all templates of up to 32 stages with 64-bit costs, whose
+    // recurrence is dearer (c5's at a micro-batch of 8: 897 us, 922 by their own)
     x.refill = 24;
     x.walk = 4;
-    x.sweeps = x.s_cap <= 16 ? 12 : 18;
+    x.sweeps = 18;
+    x.sweeps_short = narrow || x.s_cap <= 16 ? 12 : 18;
     const int64_t n_slices = (a.n + x.slice - 1) / x.slice;
     int64_t blocks = (n_slices + waves - 1) / waves;
     const int64_t most = (int64_t)cus * wgs;

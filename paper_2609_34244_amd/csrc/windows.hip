@@ -46,8 +46,17 @@ __global__ void __launch_bounds__(kWinTpl) window_kernel(DevProfile P, PriceArgs
     const bool mem_aware = (A.flags & HEDDLE_F_COMPUTE_ONLY) == 0;
     for (int g = 0; g < P.n_types; g++) cnt[g * nw] = 0;
     if (blockIdx.x == 0 && tid == 0 && A.left) A.left[0] = 0;  // length of the split search's list
+    // the first kSamples workgroups count their templates that have windows, and those
+    // templates' stages, for the search; they take tiles spread over the batch (tile b % kSamples * step + b /
+    // kSamples for workgroup b of a grid of step * kSamples and a rest)
+    const bool sampled = A.left && A.need > 0.f, counts = sampled && blockIdx.x < kSamples;
+    const uint32_t step = gridDim.x / kSamples;
+    const uint32_t tile = sampled && blockIdx.x < step * kSamples ? blockIdx.x % kSamples * step + blockIdx.x / kSamples : blockIdx.x;
+    uint32_t n_win = 0, n_stages = 0;
+    if (sampled && gridDim.x < kSamples && blockIdx.x == 0)
+        for (int i = (int)gridDim.x + tid; i < kSamples; i += nw) A.left[2 + i] = A.left[2 + kSamples + i] = 0;
 
-    for (int64_t t0 = (int64_t)blockIdx.x * nw; t0 < A.n; t0 += (int64_t)gridDim.x * nw) {
+    for (int64_t t0 = (int64_t)tile * nw; t0 < A.n; t0 += (int64_t)gridDim.x * nw) {
         // ---------------- the records of templates t0 .. t0 + nw - 1 into LDS, and
         // their ranking by stage count (bin 63 - min(S, 63))
         const int nt = A.n - t0 < nw ? (int)(A.n - t0) : nw;
@@ -163,6 +172,23 @@ __global__ void __launch_bounds__(kWinTpl) window_kernel(DevProfile P, PriceArgs
             any_ok = any_ok || fits;
         }
         if (!any_ok) close_template((uint32_t)HEDDLE_S_OOM);
+        n_win += any_ok ? 1u : 0u;
+        n_stages += any_ok ? (uint32_t)S : 0u;
+    }
+    if (counts) {
+        n_win = wave_sum(n_win);
+        n_stages = wave_sum(n_stages);
+        __syncthreads();                                       // earlier reads of bins are done
+        if ((tid & 63) == 0) {
+            bins[tid >> 6] = n_win;
+            bins[32 + (tid >> 6)] = n_stages;
+        }
+        __syncthreads();
+        if (tid < 2) {
+            uint32_t sum = 0;
+            for (int i = 0; i < nw >> 6; i++) sum += bins[32 * tid + i];
+            A.left[2 + kSamples * tid + blockIdx.x] = sum;
+        }
     }
 }
 
@@ -180,6 +206,13 @@ static int window_tile(const heddle_profile *p, const PriceArgs &a)
     return nw;
 }
 
+int window_blocks(const heddle_profile *p, const PriceArgs &a)
+{
+    const int wg = window_tile(p, a);
+    const int64_t want = (a.n + wg - 1) / wg;
+    return (int)(want < 65536 ? want : 65536);
+}
+
 int prepare_windows(const heddle_profile *p, const PriceArgs &a, int max_lds, size_t *lds)
 {
     *lds = (size_t)window_tile(p, a) * (p->dev.n_types + a.s_max + 1) * 4;
@@ -193,9 +226,7 @@ int launch_windows(const heddle_profile *p, const PriceArgs &a, size_t lds, hipS
 {
     if (a.n == 0) return HEDDLE_OK;
     const int wg = window_tile(p, a);
-    const int64_t want = (a.n + wg - 1) / wg;
-    const int blocks = (int)(want < 65536 ? want : 65536);
-    hipLaunchKernelGGL(window_kernel, dim3(blocks), dim3(wg), lds, stream, p->dev, a);
+    hipLaunchKernelGGL(window_kernel, dim3(window_blocks(p, a)), dim3(wg), lds, stream, p->dev, a);
     HEDDLE_HIP(hipGetLastError());
     return HEDDLE_OK;
 }

@@ -18,10 +18,11 @@ BUILD = os.path.join(HERE, "_build")
 SOURCES = ["profile.cpp", "windows.hip", "search.hip", "heddle_internal.h", "device_common.h", "dp_common.h", "validate.h",
            "exact_math.h"]
 LDS = 160 * 1024
+SAMPLES, LEFT_HEAD = 64, 130         # kSamples, kLeftHead
 
 
 class SplitRun(C.Structure):
-    _fields_ = [("cus", C.c_int32), ("max_lds", C.c_int32), ("preset_on", C.c_int32), ("preset", C.c_uint32), ("other", C.c_int32),
+    _fields_ = [("cus", C.c_int32), ("max_lds", C.c_int32), ("preset_on", C.c_int32), ("preset", C.c_uint32), ("need", C.c_float), ("need_slow", C.c_float), ("other", C.c_int32),
                 ("placed", C.c_int32), ("lt", C.c_int32), ("lim", C.c_int32), ("per_cu", C.c_int32), ("n_broken", C.c_int32), ("broken", C.c_char * 256)]
 
 
@@ -66,7 +67,7 @@ def lib():
     return _lib
 
 
-def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0):
+def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0, need=0, need_slow=0):
     """Window pass and split search over a workload. Returns the outputs that
     the search writes, `left` (the templates it left to the split kernel) and
     what it found broken (None: every stated condition held)."""
@@ -77,15 +78,16 @@ def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0):
     n, s_max = w.stages.shape
     t = np.float32 if flags & O.F_FP32 else np.int64
     bn, ly, st = np.empty((n, len(m)), t), np.empty((n, len(m), s_max), np.uint8), np.empty((n, len(m)), np.uint8)
-    left = np.zeros(n + 1, np.uint32)
-    r = SplitRun(cus=cus, max_lds=max_lds, preset_on=preset is not None, preset=preset or 0, other=other)
+    left = np.zeros(n + LEFT_HEAD, np.uint32)
+    r = SplitRun(cus=cus, max_lds=max_lds, preset_on=preset is not None, preset=preset or 0, other=other, need=need, need_slow=need_slow)
     d = lambda a: a.ctypes.data
     ns, recs = np.ascontiguousarray(w.n_stages, np.uint8), np.ascontiguousarray(w.stages, np.uint32)
     rc = L.lanes_split(h, n, s_max, d(ns), d(recs), d(m), len(m), flags, d(bn), d(ly), d(st), d(left), C.addressof(r))
     err = L.heddle_last_error().decode(errors="replace") if rc else ""
     L.heddle_free_profile(h)
     return {"rc": rc, "error": err, "bottleneck": bn, "layers": ly, "status": st, "left_count": int(left[0]),
-            "left": left[1:1 + min(int(left[0]), n)], "broken": r.broken.decode() if r.n_broken else None,
+            "left": left[LEFT_HEAD:LEFT_HEAD + min(int(left[0]), n)], "ran": int(left[1]),
+            "counted": int(left[2:2 + SAMPLES].sum()), "counted_stages": int(left[2 + SAMPLES:LEFT_HEAD].sum()), "broken": r.broken.decode() if r.n_broken else None,
             "n_broken": r.n_broken, "tables_in_lds": bool(r.lt), "limits_in_lds": bool(r.lim), "per_cu": r.per_cu}
 
 

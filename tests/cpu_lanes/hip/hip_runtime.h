@@ -66,7 +66,7 @@ inline int read_first(int v)
     const uint64_t *e = exchange((uint32_t)v, &there);
     return (int)(uint32_t)e[__builtin_ctzll(there)];
 }
-// row_shr 1 .. 15, row_bcast 15 and 31
+// quad_perm, row_shr 1 .. 15, mirrors of 16 and 8 lanes, row_bcast 15 and 31
 inline int update_dpp(int old, int v, int ctrl, int row_mask)
 {
     uint64_t there;
@@ -74,7 +74,9 @@ inline int update_dpp(int old, int v, int ctrl, int row_mask)
     const int l = lane(), row = l >> 4;
     if (!((row_mask >> row) & 1)) return old;
     int from = -1;
-    if (ctrl > 0x110 && ctrl < 0x120) from = (l & 15) >= ctrl - 0x110 ? l - (ctrl - 0x110) : -1;
+    if (ctrl < 0x100) from = (l & ~3) + ((ctrl >> (2 * (l & 3))) & 3);
+    else if (ctrl == 0x140 || ctrl == 0x141) from = l ^ (ctrl == 0x140 ? 15 : 7);
+    else if (ctrl > 0x110 && ctrl < 0x120) from = (l & 15) >= ctrl - 0x110 ? l - (ctrl - 0x110) : -1;
     else if (ctrl == 0x142) from = row ? row * 16 - 1 : -1;
     else if (ctrl == 0x143) from = row >= 2 ? 31 : -1;
     else abort();
@@ -117,7 +119,7 @@ template <class T, class U> T atomic_add(T *p, U v)
 #define __builtin_amdgcn_readlane lanes::read_lane
 #define __builtin_amdgcn_readfirstlane lanes::read_first
 #define __builtin_amdgcn_update_dpp(old, v, ctrl, rm, bm, bc) lanes::update_dpp(old, v, ctrl, rm)
-#define __builtin_amdgcn_mov_dpp(v, ctrl, rm, bm, bc) (abort(), 0)
+#define __builtin_amdgcn_mov_dpp(v, ctrl, rm, bm, bc) lanes::update_dpp(0, v, ctrl, rm)
 #define __builtin_amdgcn_mbcnt_lo(m, b) ((b) + (uint32_t)__builtin_popcount((m) & (lanes::lane() < 32 ? (1u << lanes::lane()) - 1 : ~0u)))
 #define __builtin_amdgcn_mbcnt_hi(m, b) ((b) + (uint32_t)__builtin_popcount((m) & (lanes::lane() < 32 ? 0u : (1u << (lanes::lane() - 32)) - 1)))
 inline float __uint_as_float(uint32_t v) { float f; memcpy(&f, &v, 4); return f; }

@@ -178,6 +178,7 @@ struct SplitRun {
     int32_t cus, max_lds;            // in: the device
     int32_t preset_on;               // in: another call writes `preset` where the list's length is kept,
     uint32_t preset;                 //     after the window pass
+    float need, need_slow;           // in: counted templates from which the search runs
     int32_t other;                   // in: not 0: the seed of another call's window pass over the same scratch
     int32_t placed, lt, lim, per_cu; // out: the search fits; tables, memory limits in LDS; wavefronts on a CU
     int32_t n_broken;
@@ -219,6 +220,9 @@ extern "C" int lanes_split(const heddle_profile *p, int64_t n, int32_t s_max, co
     a.wst = (uint32_t *)dev(plans * 4);
     a.wwin = (uint16_t *)dev(plans * win_stride(s_max) * 2);
     a.left = (uint32_t *)dev(left_bytes(n));
+    a.need = r->need;
+    a.need_slow = r->need_slow;
+    a.p2p_share = p->p2p_share;
     SearchPlan pl;
     r->placed = place_search(p->dev, a, narrow, lanes::max_lds, lanes::max_lds, lanes::cus, pl);
     r->lt = pl.lt;
@@ -242,7 +246,7 @@ extern "C" int lanes_split(const heddle_profile *p, int64_t n, int32_t s_max, co
     memcpy(bottleneck, a.bottleneck, plans * t);
     memcpy(layers, a.layers, plans * s_max);
     memcpy(status, a.status, plans);
-    memcpy(left, a.left, 4 * (size_t)(n + 1));
+    memcpy(left, a.left, left_bytes(n));
     r->n_broken = lanes::n_broken;
     snprintf(r->broken, sizeof(r->broken), "%s", lanes::n_broken ? lanes::first_broken.c_str() : "");
     for (void *q : mem) lanes::device_free(q);

@@ -80,6 +80,19 @@ def test_tables_near_the_size_of_lds(H, n_types, L, s_max, scale):
         check(H, w, flags, f"{n_types} types, L {L}, flags {flags}")
 
 
+@pytest.mark.parametrize("flags", [0, CO, F32])
+def test_few_templates_with_windows(H, flags):
+    """large batches that the recurrence takes after all: mostly invalid
+    templates, and links so slow that many searches would not settle"""
+    w = make_workload("c3_70b_dense", 200)
+    w.n_stages[np.random.default_rng(3).random(w.n) < 0.9] = 0
+    check(H, w, flags, f"mostly invalid, flags {flags}")
+    for config in ("c3_70b_dense", "c1_tiny_dense"):
+        w = make_workload(config, 200)
+        w.profile.link_bw_MBps = np.maximum(w.profile.link_bw_MBps // 40, 1)
+        check(H, w, flags, f"{config} with slow links, flags {flags}")
+
+
 def test_left_to_the_split_kernel(H):
     """templates whose cuts move up one layer at a time, so that the search
     gives them up: heavy layers that only the first stages' type can hold"""

@@ -38,6 +38,34 @@ def slow_links():
     return w
 
 
+@pytest.mark.parametrize("cus,n", [(1, 700), (20, 4300), (20, 9000)])
+def test_sample_decides(cus, n):
+    """the search runs from so many templates with windows in the window pass's
+    sample (64 workgroups, spread over the batch), and leaves the batch alone
+    below; grids of fewer workgroups, of 67 and of 70 (every tile taken once)"""
+    w = repeated(make_workload("c1_tiny_dense", 500), n)
+    assert CL.split(w, cus=cus)["ran"] == 1                    # need 0: not asked
+    g = CL.split(w, cus=cus, need=1)
+    CL.assert_split(w, g, 0)
+    has = (g["status"][:, 0] == 0) | np.isin(np.arange(n), g["left"])
+    V = g["counted"]
+    assert g["ran"] == 1 and 0 < has.sum() < n
+    assert abs(V - has.sum() * min(1, 64 * 64 / n if cus > 1 else 1)) <= (0 if cus == 1 else 0.05 * n)
+    assert 2 < g["counted_stages"] / V < 4
+    assert CL.split(w, cus=cus, need=V)["ran"] == 1
+    idle = CL.split(w, cus=cus, need=V + 1)
+    assert idle["ran"] == 0 and idle["left_count"] == 0 and ((idle["status"][:, 0] == 0xA5) == has).all()
+
+
+def test_slow_links_need_more(slow_links):
+    """transfers that outweigh the layers raise the need, fast ones do not"""
+    fast = make_workload("c3_70b_dense", 700)
+    assert CL.split(fast, need=100, need_slow=10**6)["ran"] == 1
+    V = CL.split(slow_links, need=1)["counted"]
+    assert CL.split(slow_links, need=100, need_slow=V - 101)["ran"] == 1
+    assert CL.split(slow_links, need=100, need_slow=V - 99)["ran"] == 0
+
+
 def test_left_list_holds_what_it_should(slow_links):
     g = guarded(slow_links)
     assert CL.assert_split(slow_links, g, 0) == g["left_count"] > 20
@@ -60,7 +88,7 @@ def test_left_list_reads_are_bounded():
     """the split kernel's side: a length or an entry beyond the batch ends the walk"""
     L = CL.lib()
     entry = lambda count, first, i, n: L.lanes_left_template(
-        np.array([count, first] + [7] * 8, np.uint32).ctypes.data_as(C.c_void_p), i, n)
+        np.array([count] + [0] * (CL.LEFT_HEAD - 1) + [first] + [7] * 8, np.uint32).ctypes.data_as(C.c_void_p), i, n)
     assert entry(3, 5, 0, 9) == 5 and entry(3, 5, 2, 9) == 7
     assert entry(3, 5, 3, 9) == 9                              # past the length
     assert entry(536_418_584, 5, 9, 9) == 9                    # past the list
