@@ -39,7 +39,10 @@ __device__ __forceinline__ void evaluate_plan(const DevProfile &P, const PriceAr
     bool oom = false;
     int i = 0;
     auto stage = [&](uint32_t r, uint32_t r_next, int n, int s) {
-        const int j = i + n;
+        // (a plan whose split a call that overlaps on these outputs lost holds any layer
+        // counts: no read past the rows)
+        const int j = min(i + n, P.L);
+        HEDDLE_INVARIANT(i >= 0 && i <= j && j <= P.L);
         const StageCost c = stage_cost<F32>(tab, r, (int)(r_next & 0xFF), s, S, i, j, D, Mp);
         sumT += F32 ? rne24(c.T) : c.T;
         peak = c.mem > peak ? c.mem : peak;

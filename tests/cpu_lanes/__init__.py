@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
 CSRC = os.path.join(ROOT, "paper_2609_34244_amd", "csrc")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["profile.cpp", "windows.hip", "search.hip", "heddle_internal.h", "device_common.h", "dp_common.h", "validate.h",
+SOURCES = ["profile.cpp", "windows.hip", "search.hip", "evaluate.hip", "stage_cost.h", "heddle_internal.h", "device_common.h", "dp_common.h", "validate.h",
            "exact_math.h"]
 LDS = 160 * 1024
 SAMPLES, LEFT_HEAD = 64, 130         # kSamples, kLeftHead
@@ -61,6 +61,7 @@ def lib():
         L.heddle_free_profile.argtypes = [P]
         L.heddle_last_error.restype = C.c_char_p
         L.lanes_split.argtypes = [P, C.c_int64, C.c_int32, P, P, P, C.c_int32, C.c_uint32, P, P, P, P, P]
+        L.lanes_evaluate.argtypes = [P, C.c_int64, C.c_int32, P, P, P, C.c_int32, C.c_uint32, P, P, P, P, P, P]
         L.lanes_left_template.argtypes = [P, C.c_int64, C.c_int64]
         L.lanes_left_template.restype = C.c_int64
         _lib = L
@@ -89,6 +90,21 @@ def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0, need=0, need_slo
             "left": left[LEFT_HEAD:LEFT_HEAD + min(int(left[0]), n)], "ran": int(left[1]),
             "counted": int(left[2:2 + SAMPLES].sum()), "counted_stages": int(left[2 + SAMPLES:LEFT_HEAD].sum()), "broken": r.broken.decode() if r.n_broken else None,
             "n_broken": r.n_broken, "tables_in_lds": bool(r.lt), "limits_in_lds": bool(r.lim), "per_cu": r.per_cu}
+
+
+def evaluate(w, flags, bottleneck, layers, status, max_lds=LDS):
+    """Evaluate over given splits: (iter, peak memory, status, what broke or None)"""
+    L = lib()
+    prof, h = O.OracleProfile(w.profile), C.c_void_p()
+    assert L.heddle_load_profile(prof.ref, C.byref(h)) == 0, L.heddle_last_error()
+    m, ns, recs = (np.ascontiguousarray(x, t) for x, t in ((w.m, np.int32), (w.n_stages, np.uint8), (w.stages, np.uint32)))
+    it, pk, st = np.empty_like(bottleneck), np.empty(bottleneck.shape, np.int64), np.array(status)
+    r, d = SplitRun(cus=1, max_lds=max_lds), lambda a: a.ctypes.data
+    rc = L.lanes_evaluate(h, w.n, recs.shape[1], d(ns), d(recs), d(m), len(m), flags, d(bottleneck), d(layers), d(st), d(it),
+                          d(pk), C.addressof(r))
+    L.heddle_free_profile(h)
+    assert rc == 0
+    return it, pk, st, r.broken.decode() if r.n_broken else None
 
 
 def assert_split(w, g, flags, ctx=""):

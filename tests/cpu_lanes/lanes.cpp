@@ -10,6 +10,7 @@
 #include "profile.cpp"
 #include "windows.hip"
 #include "search.hip"
+#include "evaluate.hip"
 
 namespace heddle {
 constexpr size_t kLds = 160 * 1024, kLdsTail = 16 * 1024;
@@ -250,6 +251,34 @@ extern "C" int lanes_split(const heddle_profile *p, int64_t n, int32_t s_max, co
     r->n_broken = lanes::n_broken;
     snprintf(r->broken, sizeof(r->broken), "%s", lanes::n_broken ? lanes::first_broken.c_str() : "");
     for (void *q : mem) lanes::device_free(q);
+    return rc;
+}
+
+// Evaluate over given splits: iter, peak memory and status
+extern "C" int lanes_evaluate(const heddle_profile *p, int64_t n, int32_t s_max, const uint8_t *n_stages, const uint32_t *stages,
+                              const int32_t *m, int32_t n_m, uint32_t flags, const void *bottleneck, const uint8_t *layers,
+                              uint8_t *status, void *iter, int64_t *peak_mem, SplitRun *r)
+{
+    lanes::cus = r->cus;
+    lanes::max_lds = r->max_lds;
+    lanes::n_broken = 0;
+    PriceArgs a;
+    memset(&a, 0, sizeof(a));
+    a.n = n;
+    a.s_max = s_max;
+    a.n_m = n_m;
+    a.flags = (int32_t)flags;
+    for (int k = 0; k < n_m; k++) a.m[k] = m[k];
+    a.n_stages = n_stages;
+    a.stages = stages;
+    a.bottleneck = (void *)bottleneck;
+    a.layers = (uint8_t *)layers;
+    a.status = status;
+    a.iter = iter;
+    a.peak_mem = peak_mem;
+    const int rc = launch_evaluate(p, a, nullptr);
+    r->n_broken = lanes::n_broken;
+    snprintf(r->broken, sizeof(r->broken), "%s", lanes::n_broken ? lanes::first_broken.c_str() : "");
     return rc;
 }
 

@@ -111,6 +111,23 @@ def test_windows_of_another_call(in_lds, flags):
         assert g["rc"] == 0 and g["broken"] is None, (seed, g["broken"])
 
 
+@pytest.mark.parametrize("flags", [0, F32])
+@pytest.mark.parametrize("max_lds", [CL.LDS, 4096])
+def test_evaluate_stays_inside_its_rows(flags, max_lds):
+    """Evaluate, with its tables in LDS and through the caches, 4 stages at a time
+    and one by one: the oracle's values on the oracle's splits, and no read past a
+    row where another call left any layer counts"""
+    for s_max in (16, 13):
+        w = random_instance(60 + s_max, L=40, n_types=3, s_max=s_max, n=300, max_cost=3000, moe=True, cap_scale=30.0)
+        o = O.price_plans(O.OracleProfile(w.profile), w.n_stages, w.stages, w.m, flags)
+        it, pk, st, broken = CL.evaluate(w, flags, o["bottleneck"], o["layers"], o["status"], max_lds)
+        ok = o["status"] == 0
+        assert broken is None and ok.any()
+        assert np.array_equal(st, o["status"]) and np.array_equal(pk, o["peak_mem"]) and np.array_equal(it, o["iter"])
+        layers = np.random.default_rng(s_max).integers(0, 256, o["layers"].shape).astype(np.uint8)
+        assert CL.evaluate(w, flags, o["bottleneck"], layers, o["status"], max_lds)[3] is None
+
+
 @pytest.mark.parametrize("flags", [F32, F32 | CO])
 def test_bounds_of_running_probes(slow_links, flags):
     """fp32 costs: lanes that take new templates while others are inside the probe
