@@ -22,7 +22,7 @@ SAMPLES, LEFT_HEAD = 64, 130         # kSamples, kLeftHead
 
 
 class SplitRun(C.Structure):
-    _fields_ = [("cus", C.c_int32), ("max_lds", C.c_int32), ("preset_on", C.c_int32), ("preset", C.c_uint32), ("need", C.c_float), ("need_slow", C.c_float), ("other", C.c_int32),
+    _fields_ = [("cus", C.c_int32), ("max_lds", C.c_int32), ("preset_on", C.c_int32), ("preset", C.c_uint32), ("need", C.c_float), ("need_slow", C.c_float), ("sweeps", C.c_int32), ("other", C.c_int32),
                 ("placed", C.c_int32), ("lt", C.c_int32), ("lim", C.c_int32), ("per_cu", C.c_int32), ("n_broken", C.c_int32), ("broken", C.c_char * 256)]
 
 
@@ -43,7 +43,7 @@ def build():
             with open(os.path.join(src, f), "w") as h:
                 h.write(t)
         tmp = f"{out}.{os.getpid()}"
-        subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-fPIC", "-shared", "-w", "-Wl,-Bsymbolic", "-I", src, "-o", tmp,
+        subprocess.run(["g++", "-O2", "-g", "-std=c++17", "-fPIC", "-shared", "-w", "-Wl,-Bsymbolic", "-I", src, "-o", tmp,
                         os.path.join(src, "lanes.cpp")], check=True)
         os.replace(tmp, out)
     return out
@@ -68,7 +68,7 @@ def lib():
     return _lib
 
 
-def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0, need=0, need_slow=0):
+def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0, need=0, need_slow=0, sweeps=0):
     """Window pass and split search over a workload. Returns the outputs that
     the search writes, `left` (the templates it left to the split kernel) and
     what it found broken (None: every stated condition held)."""
@@ -80,7 +80,7 @@ def split(w, flags=0, cus=1, max_lds=LDS, preset=None, other=0, need=0, need_slo
     t = np.float32 if flags & O.F_FP32 else np.int64
     bn, ly, st = np.empty((n, len(m)), t), np.empty((n, len(m), s_max), np.uint8), np.empty((n, len(m)), np.uint8)
     left = np.zeros(n + LEFT_HEAD, np.uint32)
-    r = SplitRun(cus=cus, max_lds=max_lds, preset_on=preset is not None, preset=preset or 0, other=other, need=need, need_slow=need_slow)
+    r = SplitRun(cus=cus, max_lds=max_lds, preset_on=preset is not None, preset=preset or 0, other=other, need=need, need_slow=need_slow, sweeps=sweeps)
     d = lambda a: a.ctypes.data
     ns, recs = np.ascontiguousarray(w.n_stages, np.uint8), np.ascontiguousarray(w.stages, np.uint32)
     rc = L.lanes_split(h, n, s_max, d(ns), d(recs), d(m), len(m), flags, d(bn), d(ly), d(st), d(left), C.addressof(r))

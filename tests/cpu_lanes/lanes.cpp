@@ -180,6 +180,7 @@ struct SplitRun {
     int32_t preset_on;               // in: another call writes `preset` where the list's length is kept,
     uint32_t preset;                 //     after the window pass
     float need, need_slow;           // in: counted templates from which the search runs
+    int32_t sweeps;                  // in: not 0: sweeps after which a template is left
     int32_t other;                   // in: not 0: the seed of another call's window pass over the same scratch
     int32_t placed, lt, lim, per_cu; // out: the search fits; tables, memory limits in LDS; wavefronts on a CU
     int32_t n_broken;
@@ -225,7 +226,10 @@ extern "C" int lanes_split(const heddle_profile *p, int64_t n, int32_t s_max, co
     a.need_slow = r->need_slow;
     a.p2p_share = p->p2p_share;
     SearchPlan pl;
+    const auto limit = [&](int s) { return r->sweeps ? r->sweeps : s; };
     r->placed = place_search(p->dev, a, narrow, lanes::max_lds, lanes::max_lds, lanes::cus, pl);
+    pl.x.sweeps = limit(pl.x.sweeps);
+    pl.x.sweeps_short = limit(pl.x.sweeps_short);
     r->lt = pl.lt;
     r->lim = pl.x.lim_words > 0;
     r->per_cu = pl.per_cu;

@@ -5,7 +5,7 @@ from __future__ import annotations
 import numpy as np
 
 from oracle import oracle as O
-from workloads.gen import Workload, random_instance
+from workloads.gen import Workload, pack_stage, random_instance
 
 F32 = 1
 CO = 2
@@ -71,4 +71,35 @@ def large_profile(n_types, L, s_max, scale, n):
     p.n_gpus[:] = 64
     p.layer_ns = np.ascontiguousarray(p.layer_ns * scale)
     p.mem_cap_bytes[:] = np.random.default_rng(11).integers(L, 6 * L, size=n_types)
+    return w
+
+
+def slow_outside_lds():
+    """more stage kinds than a byte holds (tables read through the caches), and
+    transfers above the layers' times"""
+    w = random_instance(21, L=100, n_types=200, s_max=12, n=40, moe=True, invalid_frac=0.1)
+    w.profile.boundary_bytes = 10**6
+    w.profile.mem_cap_bytes[:] = np.random.default_rng(11).integers(60, 2000, size=200)
+    return w
+
+
+def creeping_instance(scale=1):
+    """heavy layers that only the first stages' type can hold: cuts move up one
+    layer at a time. Three in-flight classes."""
+    w = random_instance(1, L=120, n_types=2, s_max=12, n=40, moe=False, invalid_frac=0.0, cap_scale=100.0)
+    rng = np.random.default_rng(2)
+    p = w.profile
+    p.profiled[:] = 1
+    p.layer_ns[0] = 10 * scale
+    p.layer_ns[1] = scale * np.where(rng.random(120) < 0.5, 10, 1000 + np.arange(120))[None, :]
+    p.mem_cap_bytes[:] = 1 << 40
+    p.node_size[:] = 8
+    p.n_gpus[:] = 4096
+    p.link_bw_MBps[:] = 1000
+    p.boundary_bytes = 0
+    S = rng.integers(8, 13, size=40)
+    g = rng.integers(0, 2, size=(40, 12))
+    w.m = np.array([2, 6, 64], np.int32)
+    w.n_stages = S.astype(np.uint8)
+    w.stages = np.ascontiguousarray(np.where(np.arange(12)[None] < S[:, None], pack_stage(g, 0, 0, 1), 0).astype(np.uint32))
     return w

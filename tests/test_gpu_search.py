@@ -1,15 +1,16 @@
-"""The split search (batches of at least 131,072 templates, 196,608 with fp32
-costs) against the oracle: small batches whose every template the oracle
-prices, repeated to a batch that takes the search. Every copy has to equal
-the oracle's outputs bit for bit."""
+"""The split search against the oracle: small batches whose every template the
+oracle prices, repeated to a batch that takes the search whatever its templates
+are (786,432 templates). Every copy has to equal the oracle's outputs bit for
+bit."""
 import numpy as np
 import pytest
 
-from gpu_common import CO, F32, assert_same, gpu_price, large_profile, oracle_price
-from workloads.gen import Workload, make_workload, pack_stage, random_instance
+from gpu_common import CO, F32, assert_same, creeping_instance, gpu_price, large_profile, oracle_price, slow_outside_lds
+from workloads.gen import Workload, make_workload, random_instance
 
 pytestmark = pytest.mark.gpu
-N = 196_608 + 77                                   # past both thresholds, no multiple of a slice
+N = 786_432 + 77                                   # no multiple of a slice
+N_ASKED = 196_608 + 77                             # the window pass's sample decides
 
 
 @pytest.fixture(scope="module")
@@ -21,10 +22,10 @@ def H():
     return heddle
 
 
-def check(H, w, flags, ctx):
+def check(H, w, flags, ctx, n=N):
     o = oracle_price(w, flags)
-    reps = -(-N // w.n)
-    order = np.random.default_rng(5).permutation(np.tile(np.arange(w.n), reps)[:N])
+    reps = -(-n // w.n)
+    order = np.random.default_rng(5).permutation(np.tile(np.arange(w.n), reps)[:n])
     big = Workload(name=w.name, profile=w.profile, n_stages=np.ascontiguousarray(w.n_stages[order]),
                    stages=np.ascontiguousarray(w.stages[order]), m=w.m, s_max=w.s_max)
     g = gpu_price(H, H.heddle_load_profile(w.profile), big, flags)
@@ -47,7 +48,8 @@ def test_random_instances(H, flags):
 @pytest.mark.parametrize("name,n", [("c2_7b_dense", 500), ("c3_70b_dense", 200), ("c4_moe", 300), ("c5_stress", 60)])
 @pytest.mark.parametrize("flags", [0, F32])
 def test_configs(H, name, n, flags):
-    check(H, make_workload(name, n), flags, f"{name} flags {flags}")
+    for n_batch in (N, N_ASKED):
+        check(H, make_workload(name, n), flags, f"{name} flags {flags}", n_batch)
 
 
 @pytest.mark.parametrize("flags", [0, CO, F32])
@@ -86,33 +88,47 @@ def test_few_templates_with_windows(H, flags):
     templates, and links so slow that many searches would not settle"""
     w = make_workload("c3_70b_dense", 200)
     w.n_stages[np.random.default_rng(3).random(w.n) < 0.9] = 0
-    check(H, w, flags, f"mostly invalid, flags {flags}")
+    check(H, w, flags, f"mostly invalid, flags {flags}", N_ASKED)
     for config in ("c3_70b_dense", "c1_tiny_dense"):
         w = make_workload(config, 200)
         w.profile.link_bw_MBps = np.maximum(w.profile.link_bw_MBps // 40, 1)
-        check(H, w, flags, f"{config} with slow links, flags {flags}")
+        check(H, w, flags, f"{config} with slow links, flags {flags}", N_ASKED)
 
 
-def test_left_to_the_split_kernel(H):
+@pytest.mark.parametrize("flags", [F32, F32 | CO])
+def test_slow_links_outside_lds(H, flags):
+    """transfers above the layers' times, tables read through the caches"""
+    check(H, slow_outside_lds(), flags, f"flags {flags}")
+
+
+@pytest.mark.parametrize("flags", [0, CO, F32])
+@pytest.mark.parametrize("scale", [1, 10**9])
+def test_left_to_the_split_kernel(H, scale, flags):
     """templates whose cuts move up one layer at a time, so that the search
-    gives them up: heavy layers that only the first stages' type can hold"""
-    w = random_instance(1, L=120, n_types=2, s_max=12, n=40, moe=False, invalid_frac=0.0, cap_scale=100.0)
-    rng = np.random.default_rng(2)
-    p = w.profile
-    p.profiled[:] = 1
-    p.layer_ns[0] = 10
-    p.layer_ns[1] = np.where(rng.random(120) < 0.5, 10, 1000 + np.arange(120))[None, :]
-    p.mem_cap_bytes[:] = 1 << 40
-    p.node_size[:] = 8
-    p.n_gpus[:] = 4096
-    p.link_bw_MBps[:] = 1000
-    p.boundary_bytes = 0
-    S = rng.integers(8, 13, size=40)
-    g = rng.integers(0, 2, size=(40, 12))
-    w.n_stages = S.astype(np.uint8)
-    w.stages = np.ascontiguousarray(np.where(np.arange(12)[None] < S[:, None], pack_stage(g, 0, 0, 1), 0).astype(np.uint32))
-    check(H, w, 0, "heavy layers")
-    check(H, w, F32, "heavy layers, fp32")
+    gives them up (test_search_on_cpu.py counts them)"""
+    check(H, creeping_instance(scale), flags, f"heavy layers, scale {scale}, flags {flags}")
+
+
+@pytest.mark.parametrize("flags", [0, F32, 4])
+@pytest.mark.parametrize("n", [1200, N])
+def test_addresses_off_16_bytes(H, n, flags):
+    """records at 4 and layer counts at 1, 4 and 8 bytes past a multiple of 16: the
+    paths that read and write 16 bytes are not taken"""
+    import torch
+    w = make_workload("c3_70b_dense", 200)
+    o = oracle_price(w, flags)
+    order = np.random.default_rng(5).permutation(np.arange(n) % w.n)
+    prof = H.heddle_load_profile(w.profile)
+    ns, st = H.to_device(w.n_stages[order], w.stages[order])
+    for at, byte in ((0, 1), (1, 4), (1, 0), (2, 8)):
+        rec = torch.empty(st.numel() + 4, dtype=st.dtype, device="cuda")[at:at + st.numel()].view(st.shape).copy_(st)
+        out = H.alloc_outputs(n, 1, w.s_max, flags)
+        size = out["layers"].numel()
+        out["layers"] = torch.full((size + 16,), 0xAB, dtype=torch.uint8, device="cuda")[byte:byte + size].view(out["layers"].shape)
+        assert rec.data_ptr() % 16 == 4 * at and out["layers"].data_ptr() % 16 == byte
+        H.heddle_price_plans(prof, ns, rec, [64], flags, out)
+        torch.cuda.synchronize()
+        assert_same({k: v.cpu().numpy() for k, v in out.items()}, {k: v[order] for k, v in o.items()}, flags, f"records {at}, layers {byte}")
 
 
 @pytest.mark.parametrize("chunk", [1, 15, 16, 17, 100, 0])

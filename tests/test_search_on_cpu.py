@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import cpu_lanes as CL
-from gpu_common import large_profile
+from gpu_common import creeping_instance, large_profile, slow_outside_lds
 from oracle import oracle as O
 from workloads.gen import Workload, make_workload, random_instance
 
@@ -71,6 +71,21 @@ def test_left_list_holds_what_it_should(slow_links):
     assert CL.assert_split(slow_links, g, 0) == g["left_count"] > 20
     assert len(set(g["left"].tolist())) == g["left_count"]
     assert (g["status"][g["left"]] == 8).all()                 # no split until the split kernel finds one
+
+
+@pytest.mark.parametrize("flags", [0, CO, F32, F32 | CO])
+@pytest.mark.parametrize("scale", [1, 10**9])
+def test_templates_left(scale, flags):
+    """templates are left to the split kernel where their cuts creep, and at any
+    point of a search when few sweeps are allowed: in a first probe, between
+    in-flight classes, in the last probe of fp32 costs. The others are whole."""
+    w = creeping_instance(scale)
+    assert CL.assert_split(w, CL.split(w, flags), flags, "creeping") >= 4
+    few = make_workload("c2_7b_dense", 120)
+    few.profile.layer_ns = np.ascontiguousarray(few.profile.layer_ns * (1 if scale == 1 else 1000))
+    few.m = np.array([3, 9, 64], np.int32)
+    at = [CL.assert_split(few, CL.split(few, flags, sweeps=s), flags, f"{s} sweeps") for s in (1, 3, 5, 8, 40)]
+    assert at[0] > at[1] > at[2] > at[3] > at[4] == 0
 
 
 def test_left_list_is_bounded(slow_links):
@@ -139,6 +154,10 @@ def test_bounds_of_running_probes(slow_links, flags):
         w = repeated(w, 1000)
         g = CL.split(w, flags)
         CL.assert_split(w, g, flags, f"{w.name} flags {flags}")
+    w = slow_outside_lds()
+    g = CL.split(w, flags)
+    CL.assert_split(w, g, flags, f"tables outside LDS, flags {flags}")
+    assert not g["tables_in_lds"]
 
 
 @pytest.mark.parametrize("flags", [0, CO, F32, F32 | CO])
