@@ -304,11 +304,12 @@ int heddle_best_plan(const heddle_profile *p, int64_t n, int32_t s_max,
  * that fits memory and counts zero. Synchronous.
  *   h_relaxations  HOST result.
  * With HEDDLE_F_COUNT_EVALUATED the count is of the pairs the split kernel
- * actually relaxes, which is at most the count above (large batches are split
- * by a search that relaxes no pairs; the count is then of what the recurrence
- * would relax on them): it runs the recurrence and a row's ends are taken in chunks of four by 64 >> ceil(log2 r) lanes
- * for r window rows (one lane when r >= 64), lane p taking chunks p, p + k,
- * ... from the first end; a lane stops after a chunk whose last end has a
+ * relaxes where it takes the whole batch, which is at most the count above.
+ * (Large batches are split by a search that relaxes no pairs; the count is
+ * then of what the recurrence would relax on them.) The split kernel runs the
+ * recurrence, and takes a row's ends in chunks of four by k = 64 >> ceil(log2 r)
+ * lanes for r window rows (one lane when r >= 64), lane p taking chunks p, p +
+ * k, ... from the first end; a lane stops after a chunk whose last end has a
  * stage time at or above the lane's running minimum (later ends cannot
  * lower it). Each chunk counts the ends it adds (a last chunk moved back to
  * end at the row's last end counts those from its own start); a last-stage

@@ -186,6 +186,4 @@ template <> struct Vec2<uint32_t> { typedef uint32_t type __attribute__((ext_vec
 template <> struct Vec2<uint64_t> { typedef uint64_t type __attribute__((ext_vector_type(2))); };
 template <class V> struct DPInf { static constexpr V value = ~V(0); };
 
-// all-to-all variant of a stage: none (EP = 1), inside one node, across nodes
-
 }  // namespace heddle

@@ -144,8 +144,6 @@ static int launch_evaluate_t(const heddle_profile *p, const PriceArgs &a, int ti
 {
     const int64_t want = (a.n * a.n_m + tile - 1) / tile;
     const int blocks = (int)(want < most ? want : most);
-    if (lds > 65536)
-        HEDDLE_HIP(hipFuncSetAttribute((const void *)evaluate_kernel<F32, C>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL((evaluate_kernel<F32, C>), dim3(blocks), dim3(tile), lds, stream, p->dev, a);
     HEDDLE_HIP(hipGetLastError());
     return HEDDLE_OK;

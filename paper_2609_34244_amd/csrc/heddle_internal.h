@@ -88,7 +88,7 @@ struct DevProfile {
     const uint4 *search_kind[4];     // [n_types * n_tp * n_ep]
     // the tables, one block each, copied to LDS whole (index 0: int64 ns, 1:
     // fp32 image; the 32-bit ones when the range proof allows):
-    // [search_rows][search_stride] {unused, P[0 .. L],
+    // [search_rows][search_stride] {unused (a lookup at index 0 reads before P[0]), P[0 .. L],
     // the first index of every bucket (bytes)}, then
     // [n_types * n_types + 1] p2p by type pair and a 0
     const uint32_t *search32[2];
@@ -217,7 +217,7 @@ __host__ __device__ inline int64_t left_template(const uint32_t *left, int64_t i
 
 // Launch constants of the split search.
 struct SearchArgs {
-    int32_t tab_bytes;               // bytes of the tables and kinds in LDS (0: read through the caches)
+    int32_t tab_bytes;               // bytes of the tables and kinds in LDS and of the 256 after them that index (TP, EP)
     int32_t copy_bytes, kind_off, n_kinds;   // of them the tables; where the kinds follow; how many there are
     int32_t wave_bytes;              // bytes of one wavefront's LDS region
     int32_t s_cap;                   // stage columns: min(s_max, L)

@@ -57,7 +57,6 @@ template <> struct SearchTables<uint64_t> {
     static __device__ __forceinline__ const uint64_t *get(const DevProfile &P, bool f32) { return P.search64[f32 ? 1 : 0]; }
 };
 
-
 // largest integer whose fp32 rounding is that of x
 __device__ __forceinline__ uint64_t rne24_top(uint64_t x)
 {
@@ -88,7 +87,7 @@ __global__ void __launch_bounds__(1024) search_kernel(DevProfile P, PriceArgs A,
     const int shift = sizeof(V) == 4 ? 0 : P.search_shift[f32 ? 1 : 0];
     const V b_max = (V)(INF >> 1);                             // above every stage time
     const V *gtab = SearchTables<V>::get(P, f32);
-    const V *tab;                                              // [rows][RS]: scale, least layer time, P[0 .. L], buckets
+    const V *tab;                                              // [rows][RS]: a word (read before P[0], not used), P[0 .. L], buckets
     if constexpr (LT) {
         uint4 *dst = (uint4 *)smem;
         const uint4 *src = (const uint4 *)gtab;
