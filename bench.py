@@ -3,8 +3,8 @@
 
 A step is one pass of the whole hot path over the batch: template decode and
 validation, PartitionLayers (min-max layer split), Evaluate (1F1B iteration
-time, peak memory) for every (template, m) plan -- one launch of the pricing
-kernel -- followed by the argmin over all plans. Inputs are resident in HBM
+time, peak memory) for every (template, m) plan -- one heddle_price_plans
+call -- followed by the argmin over all plans. Inputs are resident in HBM
 before the timed region. Prints one JSON line.
 
 Default workload: the 70B-like dense config (L = 80 layers, 6 GPU types,
@@ -30,6 +30,9 @@ K_MIN = 3                                   # sub, max, min per relaxation (32-b
 # gradient differences (4), and the 64-bit max / sum / max folds into the
 # split's bottleneck, total and peak memory (6)
 K_EVAL = 26
+# templates from which a batch is split by the search, which relaxes no pairs: its work is
+# taken from counters, and the recurrence's pairs are context (by fp32 costs or not)
+SEARCH_FROM = {False: 131_072, True: 196_608}
 WORKLOAD_TEXT = {
     "c1_tiny_dense": "tiny dense: L=24, 2 GPU types, 1k templates S<=4, m=16",
     "c2_7b_dense": "7B-like dense: L=32, 4 GPU types, 100k templates S<=8, m in {8,32}",
@@ -62,18 +65,19 @@ def source_hash(mode=""):
     return h.hexdigest()[:16]
 
 
-def measured_traffic(config, flags, n_plans, distribute=False):
-    """HBM bytes per launch from the committed rocprofv3 counter summary,
-    valid only for the kernel source it was measured on."""
+def measured_counters(config, flags, n_plans, distribute=False):
+    """the committed rocprofv3 counter summary of a call (HBM bytes, vector
+    instructions and lane-ops), valid only for the kernel source it was
+    measured on; empty otherwise"""
     mode = "_distribute" if distribute else ""
     path = os.path.join(ROOT, "profiles", f"price_plans_{config}{mode}_traffic.json")
     if not os.path.exists(path):
-        return None
+        return {}
     with open(path) as f:
         t = json.load(f)
     if t.get("source_sha") != source_hash(mode) or t.get("flags") != flags or t.get("plans") != n_plans:
-        return None
-    return t.get("bytes_per_launch")
+        return {}
+    return t
 
 
 def host_cpu_model():
@@ -272,8 +276,8 @@ def main():
     m = [int(x) for x in w.m]
     out = H.alloc_outputs(w.n, len(m), w.s_max, flags)
     torch.cuda.synchronize()
-    # work: the pairs the split kernel relaxes (its exit rule skips part of the
-    # window pairs); the window count is kept as context
+    # work of the recurrence: the pairs the split kernel relaxes on the whole batch
+    # (its exit rule skips part of the window pairs); the window count is context
     relax_win = H.heddle_count_work(prof, ns, st, m, flags)
     relax = relax_win if args.distribute else H.heddle_count_work(prof, ns, st, m, flags | H.HEDDLE_F_COUNT_EVALUATED)
     n_plans = w.n * len(m)
@@ -334,8 +338,14 @@ def main():
     dense_r = int((r_np * n_splits * valid).sum())
 
     kern_s = float(np.mean(kern_ms)) / 1e3
-    achieved = relax * k_unit / kern_s
-    traffic = measured_traffic(args.config, flags, n_plans, args.distribute)
+    counters = measured_counters(args.config, flags, n_plans, args.distribute)
+    traffic = counters.get("bytes_per_launch")
+    searched = not args.distribute and w.n >= SEARCH_FROM[args.fp32]
+    valu = counters.get("valu") if searched else None
+    if not searched:
+        achieved = relax * k_unit / kern_s
+    else:
+        achieved = valu["lane_ops_per_launch"] / kern_s if valu else None
     if args.distribute:
         roof = {"kernel": "distribute_kernel (one heddle_price_plans launch)",
                 "work_per_launch": relax, "work_unit": unit_name, "ops_per_unit": k_unit}
@@ -353,21 +363,35 @@ def main():
                               "mean_bottleneck_ratio": float(np.mean(bd[both] / br[both])) if both.any() else None,
                               "mean_iter_ratio": float(np.mean(it_d[both] / it_r[both])) if both.any() else None}
     else:
-        roof = {"kernel": "window_kernel + search_kernel / split_kernel + evaluate_kernel (one heddle_price_plans call)",
-                "work_per_launch": relax,
-                "work_unit": unit_name + " (pairs the split kernel's recurrence relaxes on this batch; a batch that takes "
-                             "the split search finds the same splits without relaxing them, so its rate is an equivalent one)",
-                "ops_per_unit": k_unit,
+        kernels = "window_kernel + search_kernel + split_kernel + evaluate_kernel" if searched else \
+            "window_kernel + split_kernel + evaluate_kernel"
+        roof = {"kernel": kernels + " (one heddle_price_plans call)"}
+        if searched:
+            roof.update({
+                "work_per_launch": valu["lane_ops_per_launch"] if valu else None,
+                "work_unit": "32-bit vector lane-op executed with its lane on (SQ counters of the call's kernels, "
+                             "null where none are committed for this batch and source)",
+                "ops_per_unit": 1,
+                "valu_busy": valu["insts_per_launch"] * 64 / kern_s / PEAK_LANE_OPS if valu else None,
+                "context_recurrence": {
+                    "per_launch": relax,
+                    "note": "pairs that the split kernel's recurrence would relax on the whole batch; the search finds the "
+                            "same splits without relaxing them, so this is an equivalent rate, not an achieved one",
+                    "equivalent_frac": relax * k_unit / kern_s / PEAK_LANE_OPS}})
+        else:
+            roof.update({"work_per_launch": relax, "work_unit": unit_name + " (pairs the split kernel relaxes)",
+                         "ops_per_unit": k_unit})
+        roof.update({
                 "context_window": {
                     "per_launch": relax_win,
-                    "note": "pairs of the recurrence over the row windows; the row loop's exit rule leaves "
-                            "per_launch - work_per_launch of them unrelaxed, so this is context, not an achieved rate",
+                    "note": "pairs of the recurrence over the row windows, of which the row loop's exit rule leaves "
+                            "some unrelaxed: context, not an achieved rate",
                     "equivalent_frac": relax_win * K_MIN / kern_s / PEAK_LANE_OPS},
                 "context_dense_R": {
                     "per_launch": dense_r,
-                    "note": "relaxations of the unpruned suffix recurrence over the plans whose split was computed; "
-                            "the recurrence relaxes work_per_launch of them, so this is context, not an achieved rate",
-                    "equivalent_frac": dense_r * K_MIN / kern_s / PEAK_LANE_OPS}}
+                    "note": "relaxations of the unpruned suffix recurrence over the plans whose split was computed: "
+                            "context, not an achieved rate",
+                    "equivalent_frac": dense_r * K_MIN / kern_s / PEAK_LANE_OPS}})
     result = {
         "metric": "candidate plans priced/sec (partition+evaluate) on 1 MI355X; % VALU roofline",
         "value": n_plans * args.steps / elapsed,
@@ -386,8 +410,9 @@ def main():
                    "plans": n_plans, "memory_aware": not args.compute_only, "seed": w.meta["seed"],
                    "partition": ("distribute" if args.distribute else "min-max") +
                                 (" + expert tiling" if args.tiling else "")},
-        "roofline": dict({"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_LANE_OPS / 1e12,
-                          "unit": "Tlane-op/s", "frac": achieved / PEAK_LANE_OPS, "traffic": traffic,
+        "roofline": dict({"bound": "alu", "achieved": None if achieved is None else achieved / 1e12,
+                          "peak": PEAK_LANE_OPS / 1e12, "unit": "Tlane-op/s",
+                          "frac": None if achieved is None else achieved / PEAK_LANE_OPS, "traffic": traffic,
                           "traffic_GBps": None if traffic is None else traffic / kern_s / 1e9,
                           "hbm_frac": None if traffic is None else traffic / kern_s / HBM_PEAK,
                           "kernel_ms": float(np.mean(kern_ms))}, **roof),
@@ -540,7 +565,9 @@ def run_enumerate(args, H, flags, k_unit, unit_name):
         times.append(time.perf_counter() - t0)
     step_s = float(np.mean(times))
     log(f"timed {args.steps} passes over the space: {step_s * 1e3:.1f} ms each; best {best}")
-    achieved = relax * k_unit / step_s
+    # the chunks are split by the search, which relaxes no pairs
+    searched = not args.distribute and min(chunk, total) >= SEARCH_FROM[args.fp32]
+    rate = relax * k_unit / step_s
     result = {
         "metric": "candidate plans priced/sec (partition+evaluate) on 1 MI355X; % VALU roofline",
         "value": n_plans / step_s,
@@ -560,11 +587,14 @@ def run_enumerate(args, H, flags, k_unit, unit_name):
                    "name": args.config, "templates": total, "m": m, "plans": n_plans,
                    "memory_aware": not args.compute_only,
                    "partition": "distribute" if args.distribute else "min-max"},
-        "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_LANE_OPS / 1e12, "unit": "Tlane-op/s",
-                     "frac": achieved / PEAK_LANE_OPS, "traffic": None,
+        "roofline": {"bound": "alu", "achieved": None if searched else rate / 1e12, "peak": PEAK_LANE_OPS / 1e12,
+                     "unit": "Tlane-op/s", "frac": None if searched else rate / PEAK_LANE_OPS,
+                     "equivalent_frac": rate / PEAK_LANE_OPS, "traffic": None,
                      "kernel": "whole pass (generator, split, evaluate and argmin kernels, per-chunk host syncs)",
                      "kernel_ms": step_s * 1e3, "work_per_launch": relax,
-                     "work_unit": unit_name if args.distribute else unit_name + " (pairs the split kernel relaxes)",
+                     "work_unit": unit_name if args.distribute else
+                     unit_name + (" (pairs that the recurrence would relax: an equivalent rate)" if searched
+                                  else " (pairs the split kernel relaxes)"),
                      "ops_per_unit": k_unit},
         "best_plan": {"template": best[0], "m_index": best[1], "iter": best[2], "ok_plans": best[3]},
     }
