@@ -36,13 +36,15 @@
 // word per stage in its wavefront's LDS region, so those accesses are free of
 // conflicts.
 //
-// What bounds it: vector issue and the chain of three dependent LDS reads of a
-// step (time at the end, bucket, rows around it), about 0.53 us a step with four
-// wavefronts on a SIMD. On c3 a template that fits takes 5.3 sweeps of 11.4
-// steps, where the recurrence takes about 960 vector instructions of a whole
-// wavefront: 1,000,000 templates 0.25 ms against 1.05 ms (c5, 300,000 templates x
-// 6 micro-batch counts: 2.0 ms against 7.3 ms). Half of the lanes are idle at a
-// step on average, most of them at the end of a slice (c3: 2.2 templates a lane).
+// What bounds it: the slices that take longest, and within them vector issue and the
+// chain of three dependent LDS reads of a step (time at the end, bucket, rows around
+// it). On c3 (1,000,000 templates, 16 wavefronts on a CU, a slice each) the vector units
+// are busy 54% of the launch with 37.8 of 64 lanes on, 2.8 of a SIMD's 4 wavefronts are
+// alive on average, and LDS is busy 32%, 44% of that with bank conflicts of the random
+// reads (c5, 11 wavefronts: 42%, 30.4 lanes, 2.35 of 2.75, 23%, 50%). A template that
+// fits takes 5.3 sweeps of one step per stage, where the recurrence takes about 960
+// vector instructions of a whole wavefront: 0.23 ms against 1.05 ms (c5, 300,000
+// templates x 6 micro-batch counts: 2.0 ms against 7.3 ms).
 #include <cstring>
 
 #include "dp_common.h"
