@@ -88,7 +88,10 @@ constexpr float kSearchWin4 = 32000, kSearchWin = 56000, kSearchSlow = 130000, k
 // loops carry no test of them.
 // COUNT: 0 prices; 1 counts the relaxations over the windows (no DP); 2 runs the DP
 // and counts the (row, end) pairs it relaxes under the row loop's exit rule
-template <class V, bool F32, int COUNT, int NS, bool MA, bool M1>
+// SEARCHED: launched behind the split search, for the templates it left or, where it
+// did not run, for all (a variant of its own: the test of it in the loop over the
+// templates took 5% where they are short, c1 of 100,000 48.8 us against 46.5)
+template <class V, bool F32, int COUNT, int NS, bool MA, bool M1, bool SEARCHED>
 __global__ void __launch_bounds__(64, sizeof(V) == 4 ? 8 : 4) split_kernel(DevProfile P, PriceArgs A)
 {
     typedef typename Vec2<V>::type V2;
@@ -138,7 +141,7 @@ __global__ void __launch_bounds__(64, sizeof(V) == 4 ? 8 : 4) split_kernel(DevPr
         h += gridDim.x;
         return left_template(A.left, i, A.n);
     };
-    const bool listed = A.left && A.left[1] != 0;
+    const bool listed = SEARCHED && A.left[1] != 0;
     if (listed) t = next_left();
     int64_t t_next = t;
     int S_next = 0;
@@ -533,6 +536,21 @@ static size_t window_scratch_bytes(int64_t n, int32_t n_m, int32_t s_max)
     return ((plans * sizeof(uint32_t) + 255) & ~size_t(255)) + plans * win_stride(s_max) * sizeof(uint16_t);
 }
 
+template <class V, bool F32, int COUNT, bool SEARCHED> static const void *split_variant(const PriceArgs &a, int L)
+{
+    // time-prefix slots of 64 entries held in registers: 2 cover L + 1 <= 128
+    const bool ma = (a.flags & HEDDLE_F_COMPUTE_ONLY) == 0;
+    if (a.n_m == 1)
+        return L + 1 <= 128 ? (ma ? (const void *)split_kernel<V, F32, COUNT, 2, true, true, SEARCHED>
+                                  : (const void *)split_kernel<V, F32, COUNT, 2, false, true, SEARCHED>)
+                            : (ma ? (const void *)split_kernel<V, F32, COUNT, 4, true, true, SEARCHED>
+                                  : (const void *)split_kernel<V, F32, COUNT, 4, false, true, SEARCHED>);
+    return L + 1 <= 128 ? (ma ? (const void *)split_kernel<V, F32, COUNT, 2, true, false, SEARCHED>
+                              : (const void *)split_kernel<V, F32, COUNT, 2, false, false, SEARCHED>)
+                        : (ma ? (const void *)split_kernel<V, F32, COUNT, 4, true, false, SEARCHED>
+                              : (const void *)split_kernel<V, F32, COUNT, 4, false, false, SEARCHED>);
+}
+
 template <class V, bool F32, int COUNT>
 static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t stream)
 {
@@ -574,20 +592,6 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
     const int wpb = 1;
     const size_t lds = (size_t)wpb * a.lds_per_wave;
     if (lds > (size_t)max_lds) return fail(HEDDLE_E_RANGE, "DP table of this (L, s_max) does not fit in LDS");
-    // time-prefix slots of 64 entries held in registers: 2 cover L + 1 <= 128
-    const bool ma = (a.flags & HEDDLE_F_COMPUTE_ONLY) == 0;
-    const void *kern;
-    if (a.n_m == 1)
-        kern = L + 1 <= 128 ? (ma ? (const void *)split_kernel<V, F32, COUNT, 2, true, true>
-                                  : (const void *)split_kernel<V, F32, COUNT, 2, false, true>)
-                            : (ma ? (const void *)split_kernel<V, F32, COUNT, 4, true, true>
-                                  : (const void *)split_kernel<V, F32, COUNT, 4, false, true>);
-    else
-        kern = L + 1 <= 128 ? (ma ? (const void *)split_kernel<V, F32, COUNT, 2, true, false>
-                                  : (const void *)split_kernel<V, F32, COUNT, 2, false, false>)
-                            : (ma ? (const void *)split_kernel<V, F32, COUNT, 4, true, false>
-                                  : (const void *)split_kernel<V, F32, COUNT, 4, false, false>);
-    if (lds > 65536) HEDDLE_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     size_t w_lds = 0;
     const int rc = prepare_windows(p, a, max_lds, &w_lds);
     if (rc != HEDDLE_OK) return rc;
@@ -629,6 +633,10 @@ static int launch_split(const heddle_profile *p, PriceArgs &a, hipStream_t strea
         a.need_slow = part * (F32 ? kSearchSlowF32 : kSearchSlow);
         a.p2p_share = p->p2p_share;
     }
+    const void *kern;
+    if constexpr (COUNT == 0) kern = search ? split_variant<V, F32, 0, true>(a, L) : split_variant<V, F32, 0, false>(a, L);
+    else kern = split_variant<V, F32, COUNT, false>(a, L);
+    if (lds > 65536) HEDDLE_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     unsigned char *buf = nullptr;
     if (a.ext_scratch) {
         if (bytes > a.ext_bytes) return fail(HEDDLE_E_RANGE, "window scratch exceeds the fixed buffer");
